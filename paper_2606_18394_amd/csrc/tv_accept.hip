@@ -115,50 +115,39 @@ __device__ __forceinline__ void see_chunk(Best& best, const uint4& w, unsigned i
   }
 }
 
-// The key of one (row, split) slice, returned to every thread.
-template <bool F32, bool VEC>
+// The key of one (row, split) slice, returned to every thread: chunks
+// [split * cps, ...) of the row; the few elements outside the row's chunks are
+// split 0's, one per thread, requested with its first chunks.
+template <bool F32>
 __device__ __forceinline__ unsigned long long scan_slice(const AcceptArgs& a, int row, int split) {
-  constexpr int E = VEC ? (F32 ? 4 : 8) : 1;  // elements per chunk
   constexpr int L = kAcceptScanLoads;
   const int tid = threadIdx.x;
-  const long long nchunks = ((long long)a.V + E - 1) / E;
+  const char* base = (const char*)a.logits + (size_t)row * a.V * (F32 ? 4 : 2);
+  const RowSpan<F32> rs(base, a.V);
   const long long c0 = (long long)split * a.cps;
-  const long long c1 = c0 + a.cps < nchunks ? c0 + a.cps : nchunks;
+  const long long c1 = c0 + a.cps < rs.chunks ? c0 + a.cps : rs.chunks;
 
-  Best best{0.f, 0u, false};
-  if (VEC) {
-    const uint4* base = reinterpret_cast<const uint4*>(
-        (const char*)a.logits + (size_t)row * a.V * (F32 ? 4 : 2));
-    // rounds of L loads per thread, all issued before any is used
-    for (long long c = c0 + tid; c < c1; c += (long long)L * kAcceptScanThreads) {
-      uint4 w[L];
+  Best best{0.f, 0u, false}, spare{0.f, 0u, false};
+  if (split == 0 && rs.spare(tid) < a.V)
+    spare.see(load_logit_stream<F32>(base, rs.spare(tid)), (unsigned int)rs.spare(tid));
+  // rounds of L loads per thread, all issued before any is used
+  for (long long c = c0 + tid; c < c1; c += (long long)L * kAcceptScanThreads) {
+    uint4 w[L];
 #pragma unroll
-      for (int u = 0; u < L; ++u) {
-        const long long cu = c + (long long)u * kAcceptScanThreads;
-        if (cu < c1) w[u] = load_stream(base + cu);
-      }
-#pragma unroll
-      for (int u = 0; u < L; ++u) {
-        const long long cu = c + (long long)u * kAcceptScanThreads;
-        if (cu < c1) see_chunk<F32>(best, w[u], (unsigned int)(cu * E));
-      }
+    for (int u = 0; u < L; ++u) {
+      const long long cu = c + (long long)u * kAcceptScanThreads;
+      if (cu < c1) w[u] = rs.load(cu);
     }
-  } else {
-    for (long long c = c0 + tid; c < c1; c += kAcceptScanThreads) {
-      float x;
-      if (F32) {
-        x = load_stream(reinterpret_cast<const float*>(a.logits) + (size_t)row * a.V + c);
-      } else {
-        const unsigned short h =
-            load_stream(reinterpret_cast<const unsigned short*>(a.logits) + (size_t)row * a.V + c);
-        x = __uint_as_float((unsigned int)h << 16);
-      }
-      best.see(x, (unsigned int)c);
+#pragma unroll
+    for (int u = 0; u < L; ++u) {
+      const long long cu = c + (long long)u * kAcceptScanThreads;
+      if (cu < c1) see_chunk<F32>(best, w[u], (unsigned int)rs.index(cu));
     }
   }
 
   __shared__ unsigned long long red[kAcceptScanThreads / 64];
   unsigned long long key = best.any ? make_key(best.v, best.i) : 0ull;
+  if (spare.any) key = umax64(key, make_key(spare.v, spare.i));
   key = wave_max_u64(key);
   if ((tid & 63) == 0) red[tid >> 6] = key;
   __syncthreads();
@@ -280,11 +269,11 @@ __device__ __forceinline__ void accept_sequence(const AcceptArgs& a, int b, cons
 }
 
 // First kernel: the key of every (row, split).
-template <bool F32, bool VEC>
+template <bool F32>
 __global__ __launch_bounds__(kAcceptScanThreads) void accept_scan(AcceptArgs a) {
   const int row = blockIdx.x / a.nsplit;
   const int split = blockIdx.x % a.nsplit;
-  const unsigned long long key = scan_slice<F32, VEC>(a, row, split);
+  const unsigned long long key = scan_slice<F32>(a, row, split);
   if (threadIdx.x == 0) a.part[(size_t)row * a.nsplit + split] = key;
 }
 
@@ -537,9 +526,7 @@ hipError_t launch_accept(const void* logits, int f32, const int32_t* draft, cons
                          int B, int N, int V, int Dmax, int32_t* accept_len, int32_t* path,
                          int32_t* tgt_out, void* ws, hipStream_t st) {
   const int esize = f32 ? 4 : 2;
-  const int velems = 16 / esize;
-  const bool vec = ((uintptr_t)logits % 16 == 0) && ((size_t)V * esize % 16 == 0);
-  const AcceptPlan p = accept_plan(B, N, V, esize, vec ? velems : 1);
+  const AcceptPlan p = accept_plan(B, N, V, esize, 16 / esize);
   AcceptArgs a;
   a.logits = logits;
   a.draft = draft;
@@ -555,13 +542,8 @@ hipError_t launch_accept(const void* logits, int f32, const int32_t* draft, cons
   a.nsplit = p.nsplit;
   a.cps = p.chunks_per_split;
   const dim3 g(p.grid), t(kAcceptScanThreads);
-  if (f32) {
-    if (vec) hipLaunchKernelGGL((accept_scan<true, true>), g, t, 0, st, a);
-    else hipLaunchKernelGGL((accept_scan<true, false>), g, t, 0, st, a);
-  } else {
-    if (vec) hipLaunchKernelGGL((accept_scan<false, true>), g, t, 0, st, a);
-    else hipLaunchKernelGGL((accept_scan<false, false>), g, t, 0, st, a);
-  }
+  if (f32) hipLaunchKernelGGL(accept_scan<true>, g, t, 0, st, a);
+  else hipLaunchKernelGGL(accept_scan<false>, g, t, 0, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // One wave per sequence up to 128 nodes (the plans' split counts fit its

@@ -216,9 +216,9 @@ __device__ __forceinline__ int best_head_lane(float v, int i) {
 // fall back to the per-thread lists and W rounds of workgroup argmax.
 constexpr int kTopwCand = kScanThreads;
 
-template <bool F32, bool VEC, int K, bool ONE>
+template <bool F32, int K, bool ONE>
 __global__ __launch_bounds__(kScanThreads) void topw_scan(TopwArgs a) {
-  constexpr int E = VEC ? (F32 ? 4 : 8) : 1;  // elements per chunk
+  constexpr int E = F32 ? 4 : 8;  // elements per chunk
   constexpr int L = kScanLoadsPerThread;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   __shared__ int s_ncand;
@@ -228,9 +228,10 @@ __global__ __launch_bounds__(kScanThreads) void topw_scan(TopwArgs a) {
   int ncand = 0;
   const int row = blockIdx.x / a.nsplit;
   const int split = blockIdx.x % a.nsplit;
-  const long long nchunks = ((long long)a.V + E - 1) / E;
-  const long long c0 = (long long)split * a.cps;
-  const long long c1 = c0 + a.cps < nchunks ? c0 + a.cps : nchunks;
+  const char* rowp = (const char*)a.logits + (size_t)row * a.V * (F32 ? 4 : 2);
+  const RowSpan<F32> rs(rowp, a.V);
+  const long long c0 = min((long long)split * a.cps, (long long)rs.chunks);
+  const long long c1 = min(c0 + a.cps, (long long)rs.chunks);
   const int W = a.W;
 
   TopList<K> top;
@@ -239,9 +240,16 @@ __global__ __launch_bounds__(kScanThreads) void topw_scan(TopwArgs a) {
   // tau: a lower bound on the slice's W-th largest value, known after the
   // first round; only elements >= tau reach the (divergent) list insertion
   float tau = -INFINITY;
-  const char* rowp = (const char*)a.logits + (size_t)row * a.V * (F32 ? 4 : 2);
-  // rounds are uniform across the workgroup (the first ends at a barrier)
-  for (long long cb = c0; cb < c1; cb += (long long)L * kScanThreads) {
+  // The few elements outside the row's chunks are the last split's, one per
+  // thread: in its first round where it lies before the chunks, in its last
+  // where it lies behind them (a thread's elements come in index order).
+  const bool spare = split == a.nsplit - 1 && rs.spare(tid) < a.V;
+  const int xi = (int)rs.spare(tid);
+  const float xt = spare ? load_logit_stream<F32>(rowp, xi) : -INFINITY;
+  // rounds are uniform across the workgroup (the first ends at a barrier and
+  // always runs, also for a slice without whole chunks)
+  long long cb = c0;
+  do {
     const long long c = cb + tid;
     // all L loads are issued first (past the end: the last chunk again),
     // then decoded with the padding replaced by -inf bit patterns, so the
@@ -252,13 +260,7 @@ __global__ __launch_bounds__(kScanThreads) void topw_scan(TopwArgs a) {
     for (int u = 0; u < L; ++u) {
       const long long cu = c + (long long)u * kScanThreads;
       const long long cl = cu < c1 ? cu : c1 - 1;
-      if (VEC) {
-        raw[u] = load_stream(reinterpret_cast<const uint4*>(rowp) + cl);
-      } else if (F32) {
-        raw[u].x = load_stream(reinterpret_cast<const unsigned int*>(rowp) + cl);
-      } else {
-        raw[u].x = (unsigned int)load_stream(reinterpret_cast<const unsigned short*>(rowp) + cl) << 16;
-      }
+      if (rs.chunks > 0) raw[u] = rs.load(cl);
     }
     float x[L][E];
 #pragma unroll
@@ -266,22 +268,20 @@ __global__ __launch_bounds__(kScanThreads) void topw_scan(TopwArgs a) {
       const bool in = c + (long long)u * kScanThreads < c1;
       const unsigned int ws[4] = {in ? raw[u].x : kNegInf, in ? raw[u].y : kNegInf,
                                   in ? raw[u].z : kNegInf, in ? raw[u].w : kNegInf};
-      if (VEC) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          if (F32) {
-            x[u][k] = __uint_as_float(ws[k]);
-          } else {
-            x[u][2 * k] = __uint_as_float(ws[k] << 16);
-            x[u][2 * k + 1] = __uint_as_float(ws[k] & 0xFFFF0000u);
-          }
+      for (int k = 0; k < 4; ++k) {
+        if (F32) {
+          x[u][k] = __uint_as_float(ws[k]);
+        } else {
+          x[u][2 * k] = __uint_as_float(ws[k] << 16);
+          x[u][2 * k + 1] = __uint_as_float(ws[k] & 0xFFFF0000u);
         }
-      } else {
-        x[u][0] = __uint_as_float(in ? raw[u].x : 0xFF800000u);
       }
     }
+    const bool extra = spare && (tid < rs.head ? cb == c0 : cb + (long long)L * kScanThreads >= c1);
+    const float xe = extra ? xt : -INFINITY;
     float bmu[L];  // maximum of each load
-    float bm = -INFINITY;
+    float bm = xe;
 #pragma unroll
     for (int u = 0; u < L; ++u) {
       bmu[u] = x[u][0];
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(kScanThreads) void topw_scan(TopwArgs a) {
     }
     if (bm != -INFINITY) {  // a thread past the slice end has only padding
       const float mn = fmaxf(m, bm);
-      float bs = 0.f;
+      float bs = extra ? __expf(xe - mn) : 0.f;
 #pragma unroll
       for (int u = 0; u < L; ++u)
 #pragma unroll
@@ -333,9 +333,16 @@ __global__ __launch_bounds__(kScanThreads) void topw_scan(TopwArgs a) {
                 const int slot = atomicAdd(&s_ncand, 1);
                 if (slot < kTopwCand) {
                   s_cv[slot] = x[u][e];
-                  s_ci[slot] = (int)(cu * E + e);
+                  s_ci[slot] = rs.index(cu) + e;
                 }
               }
+          }
+        }
+        if (extra && xe >= tau) {
+          const int slot = atomicAdd(&s_ncand, 1);
+          if (slot < kTopwCand) {
+            s_cv[slot] = xe;
+            s_ci[slot] = xi;
           }
         }
       }
@@ -344,15 +351,19 @@ __global__ __launch_bounds__(kScanThreads) void topw_scan(TopwArgs a) {
     }
     // padding (-inf) never passes; equal values keep the earlier index
     if ((!ONE || ncand > kTopwCand) && bm >= tau && bm > top.thr()) {
+      const bool before = tid < rs.head;
+      if (extra && before && xe >= tau && xe > top.thr()) top.insert(xe, xi);
 #pragma unroll
       for (int u = 0; u < L; ++u) {
         const long long cu = c + (long long)u * kScanThreads;
 #pragma unroll
         for (int e = 0; e < E; ++e)
-          if (x[u][e] >= tau && x[u][e] > top.thr()) top.insert(x[u][e], (int)(cu * E + e));
+          if (x[u][e] >= tau && x[u][e] > top.thr()) top.insert(x[u][e], rs.index(cu) + e);
       }
+      if (extra && !before && xe >= tau && xe > top.thr()) top.insert(xe, xi);
     }
-  }
+    cb += (long long)L * kScanThreads;
+  } while (cb < c1);
 
   // workgroup: (m, s) by shuffles and LDS, the top-W by W rounds of argmax
   __shared__ float red_m[kScanThreads / 64], red_s[kScanThreads / 64];
@@ -450,37 +461,23 @@ __global__ __launch_bounds__(64) void topw_finish(TopwArgs a) {
   }
 }
 
-template <int K, bool ONE>
-static void launch_topw_scan_k(bool f32, bool vec, dim3 g, dim3 t, hipStream_t st,
-                               const TopwArgs& a) {
-  if (f32) {
-    if (vec) hipLaunchKernelGGL((topw_scan<true, true, K, ONE>), g, t, 0, st, a);
-    else hipLaunchKernelGGL((topw_scan<true, false, K, ONE>), g, t, 0, st, a);
-  } else {
-    if (vec) hipLaunchKernelGGL((topw_scan<false, true, K, ONE>), g, t, 0, st, a);
-    else hipLaunchKernelGGL((topw_scan<false, false, K, ONE>), g, t, 0, st, a);
-  }
-}
-
 template <bool ONE>
-static void launch_topw_scan_one(bool f32, bool vec, int K, dim3 g, dim3 t, hipStream_t st,
-                                 const TopwArgs& a) {
-  if (K == 4) launch_topw_scan_k<4, ONE>(f32, vec, g, t, st, a);
-  else if (K == 8) launch_topw_scan_k<8, ONE>(f32, vec, g, t, st, a);
-  else launch_topw_scan_k<kTopwMax, ONE>(f32, vec, g, t, st, a);
-}
-
-static void launch_topw_scan(bool f32, bool vec, int K, bool one, dim3 g, dim3 t,
-                             hipStream_t st, const TopwArgs& a) {
-  if (one) launch_topw_scan_one<true>(f32, vec, K, g, t, st, a);
-  else launch_topw_scan_one<false>(f32, vec, K, g, t, st, a);
+static void launch_topw_scan(bool f32, int K, dim3 g, dim3 t, hipStream_t st, const TopwArgs& a) {
+  if (f32) {
+    if (K == 4) hipLaunchKernelGGL((topw_scan<true, 4, ONE>), g, t, 0, st, a);
+    else if (K == 8) hipLaunchKernelGGL((topw_scan<true, 8, ONE>), g, t, 0, st, a);
+    else hipLaunchKernelGGL((topw_scan<true, kTopwMax, ONE>), g, t, 0, st, a);
+  } else {
+    if (K == 4) hipLaunchKernelGGL((topw_scan<false, 4, ONE>), g, t, 0, st, a);
+    else if (K == 8) hipLaunchKernelGGL((topw_scan<false, 8, ONE>), g, t, 0, st, a);
+    else hipLaunchKernelGGL((topw_scan<false, kTopwMax, ONE>), g, t, 0, st, a);
+  }
 }
 
 hipError_t launch_topw(const void* logits, int f32, int B, int Nd, int V, int W, int32_t* tok,
                        float* logp, void* ws, hipStream_t st) {
   const int esize = f32 ? 4 : 2;
-  const bool vec = ((uintptr_t)logits % 16 == 0) && ((size_t)V * esize % 16 == 0);
-  const TopwPlan p = topw_plan(B, Nd, V, vec ? 16 / esize : 1);
+  const TopwPlan p = topw_plan(B, Nd, V, 16 / esize);
   TopwArgs a;
   a.logits = logits;
   a.tok = tok;
@@ -495,7 +492,8 @@ hipError_t launch_topw(const void* logits, int f32, int B, int Nd, int V, int W,
   const int K = W <= 4 ? 4 : (W <= 8 ? 8 : 16);
   // one load round per workgroup: every split's slice fits in one
   const bool one = p.chunks_per_split <= (long long)kScanThreads * kScanLoadsPerThread;
-  launch_topw_scan(f32 != 0, vec, K, one, g, t, st, a);
+  if (one) launch_topw_scan<true>(f32 != 0, K, g, t, st, a);
+  else launch_topw_scan<false>(f32 != 0, K, g, t, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (K == 4) hipLaunchKernelGGL(topw_finish<4>, dim3(a.rows), dim3(64), 0, st, a);

@@ -106,18 +106,20 @@ __device__ __forceinline__ float load_logit(const void* base, size_t idx) {
   return __uint_as_float((unsigned int)reinterpret_cast<const unsigned short*>(base)[idx] << 16);
 }
 
-// 8 consecutive logits from a 16-byte aligned position (two loads for fp32)
+typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+
+// 8 consecutive logits from any position (two loads for fp32)
 template <bool F32>
 __device__ __forceinline__ void load8(const void* base, size_t idx, float (&x)[8]) {
+  const u32x4_any* p =
+      reinterpret_cast<const u32x4_any*>((const char*)base + idx * (F32 ? 4 : 2));
   if (F32) {
-    const uint4* p = reinterpret_cast<const uint4*>(reinterpret_cast<const float*>(base) + idx);
-    const uint4 a = p[0], b = p[1];
+    const u32x4_any a = p[0], b = p[1];
     const unsigned int w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
 #pragma unroll
     for (int k = 0; k < 8; ++k) x[k] = __uint_as_float(w[k]);
   } else {
-    const uint4 a =
-        *reinterpret_cast<const uint4*>(reinterpret_cast<const unsigned short*>(base) + idx);
+    const u32x4_any a = p[0];
     const unsigned int w[4] = {a.x, a.y, a.z, a.w};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -155,84 +157,81 @@ __device__ __forceinline__ unsigned long long wave_max_key(unsigned long long k)
 
 // ------------------------------------------------------------ lse_scan
 
-// (max, sum exp) of x / T over elements [x0, x1) of a row, into m and s,
-// which start at (-inf, 0); x0 and x1 are multiples of 8 (or x1 = V) so that
-// vectorised rows read whole 16-byte chunks of either dtype
+// (max, sum exp) of x / T over one split's share of a row, into m and s, which
+// start at (-inf, 0): its 16-byte chunks, and in the last split the few
+// elements outside the row's chunks, one per thread, requested with the first
+// chunks.
+//
+// In base-2 units: with c2 = log2(e) / T a weight is exp2(x * c2 - m2) (one
+// fma and one exp2 per logit), m2 the running maximum of x * c2; the batch
+// maximum is taken on the raw logits (c2 > 0 keeps the order).  m is returned
+// in the natural units of x / T.
 template <bool F32>
-__device__ __forceinline__ void lse_slice(const void* rowp, long long x0, long long x1, bool vec,
-                                          float invT, float& m, float& s) {
+__device__ __forceinline__ void lse_slice(const SampleArgs& a, int row, int split, float& m,
+                                          float& s) {
   constexpr int E = F32 ? 4 : 8;  // elements per 16-byte chunk
   constexpr int L = kLseScanLoads;
   const int tid = threadIdx.x;
-  if (vec) {
-    // In base-2 units: with c2 = log2(e) / T a weight is exp2(x * c2 - m2)
-    // (one fma and one exp2 per logit), m2 the running maximum of x * c2;
-    // the batch maximum is taken on the raw logits (c2 > 0 keeps the order).
-    // m is returned in the natural units of x / T.
-    const float c2 = invT * 1.4426950408889634f;
-    float m2 = -INFINITY;
-    const long long c0 = x0 / E, c1 = (x1 + E - 1) / E;
-    const uint4* base = reinterpret_cast<const uint4*>(rowp);
-    for (long long c = c0 + tid; c < c1; c += (long long)L * kLseScanThreads) {
-      // all L loads are issued first (past the end: the last chunk again),
-      // then decoded with the padding replaced by -inf bit patterns, so the
-      // loads are in flight together
-      constexpr unsigned int kNegInf = F32 ? 0xFF800000u : 0xFF80FF80u;
-      uint4 raw[L];
+  const float c2 = a.invT * 1.4426950408889634f;
+  const char* rowp = (const char*)a.logits + (size_t)row * a.V * (F32 ? 4 : 2);
+  const RowSpan<F32> rs(rowp, a.V);
+  const long long c0 = split * (a.eps / E);
+  const long long c1 = min(c0 + a.eps / E, (long long)rs.chunks);
+  const bool spare = split == a.nsplit - 1 && rs.spare(tid) < a.V;
+  const float xt = spare ? load_logit_stream<F32>(rowp, rs.spare(tid)) : -INFINITY;
+  float m2 = -INFINITY;
+  for (long long c = c0 + tid; c < c1; c += (long long)L * kLseScanThreads) {
+    // all L loads are issued first (past the end: the last chunk again),
+    // then decoded with the padding replaced by -inf bit patterns, so the
+    // loads are in flight together
+    constexpr unsigned int kNegInf = F32 ? 0xFF800000u : 0xFF80FF80u;
+    uint4 raw[L];
 #pragma unroll
-      for (int u = 0; u < L; ++u) {
-        const long long cu = c + (long long)u * kLseScanThreads;
-        raw[u] = load_stream(base + (cu < c1 ? cu : c1 - 1));
-      }
-      float x[L][E];
+    for (int u = 0; u < L; ++u) {
+      const long long cu = c + (long long)u * kLseScanThreads;
+      raw[u] = rs.load(cu < c1 ? cu : c1 - 1);
+    }
+    float x[L][E];
 #pragma unroll
-      for (int u = 0; u < L; ++u) {
-        const bool in = c + (long long)u * kLseScanThreads < c1;
-        const unsigned int ws[4] = {in ? raw[u].x : kNegInf, in ? raw[u].y : kNegInf,
-                                    in ? raw[u].z : kNegInf, in ? raw[u].w : kNegInf};
+    for (int u = 0; u < L; ++u) {
+      const bool in = c + (long long)u * kLseScanThreads < c1;
+      const unsigned int ws[4] = {in ? raw[u].x : kNegInf, in ? raw[u].y : kNegInf,
+                                  in ? raw[u].z : kNegInf, in ? raw[u].w : kNegInf};
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          if (F32) {
-            x[u][k] = __uint_as_float(ws[k]);
-          } else {
-            x[u][2 * k] = __uint_as_float(ws[k] << 16);
-            x[u][2 * k + 1] = __uint_as_float(ws[k] & 0xFFFF0000u);
-          }
+      for (int k = 0; k < 4; ++k) {
+        if (F32) {
+          x[u][k] = __uint_as_float(ws[k]);
+        } else {
+          x[u][2 * k] = __uint_as_float(ws[k] << 16);
+          x[u][2 * k + 1] = __uint_as_float(ws[k] & 0xFFFF0000u);
         }
       }
-      float bm = -INFINITY;
-#pragma unroll
-      for (int u = 0; u < L; ++u)
-#pragma unroll
-        for (int e = 0; e < E; ++e) bm = fmaxf(bm, x[u][e]);
-      if (bm == -INFINITY) continue;
-      const float mn = fmaxf(m2, bm * c2);
-      float bs = 0.f;
-#pragma unroll
-      for (int u = 0; u < L; ++u)
-#pragma unroll
-        for (int e = 0; e < E; ++e) bs += __builtin_amdgcn_exp2f(fmaf(x[u][e], c2, -mn));
-      s = (m2 == -INFINITY ? 0.f : s * __builtin_amdgcn_exp2f(m2 - mn)) + bs;
-      m2 = mn;
     }
-    m = m2 == -INFINITY ? -INFINITY : m2 * 0.6931471805599453f;
-  } else {
-    for (long long c = x0 + tid; c < x1; c += kLseScanThreads) {
-      const float x = load_logit<F32>(rowp, (size_t)c) * invT;
-      lse_merge2(m, s, x, 1.f);
-    }
+    float bm = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < L; ++u)
+#pragma unroll
+      for (int e = 0; e < E; ++e) bm = fmaxf(bm, x[u][e]);
+    if (bm == -INFINITY) continue;
+    const float mn = fmaxf(m2, bm * c2);
+    float bs = 0.f;
+#pragma unroll
+    for (int u = 0; u < L; ++u)
+#pragma unroll
+      for (int e = 0; e < E; ++e) bs += __builtin_amdgcn_exp2f(fmaf(x[u][e], c2, -mn));
+    s = (m2 == -INFINITY ? 0.f : s * __builtin_amdgcn_exp2f(m2 - mn)) + bs;
+    m2 = mn;
   }
+  m = m2 == -INFINITY ? -INFINITY : m2 * 0.6931471805599453f;
+  if (spare) lse_merge2(m, s, xt * a.invT, 1.f);
 }
 
 template <bool F32>
-__global__ __launch_bounds__(kLseScanThreads) void lse_scan(SampleArgs a, int vec) {
+__global__ __launch_bounds__(kLseScanThreads) void lse_scan(SampleArgs a) {
   const int row = blockIdx.x / a.nsplit, split = blockIdx.x % a.nsplit;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const long long x0 = (long long)split * a.eps;
-  const long long x1 = x0 + a.eps < a.V ? x0 + a.eps : a.V;
   float m = -INFINITY, s = 0.f;
-  const char* rowp = (const char*)a.logits + (size_t)row * a.V * (F32 ? 4 : 2);
-  lse_slice<F32>(rowp, x0, x1, vec != 0, a.invT, m, s);
+  lse_slice<F32>(a, row, split, m, s);
   __shared__ float rm[kLseScanThreads / 64], rs[kLseScanThreads / 64];
   // pair merges inside each row of 16 lanes on DPP exchanges (a merge is
   // symmetric, so both lanes of a pair hold the same state), then the rows
@@ -268,7 +267,7 @@ constexpr int kNodesPerThread = kMaxNodes / kSampleThreads;
 static_assert(kMaxNodes % kSampleThreads == 0, "whole node batches per thread");
 
 template <bool F32>
-__global__ __launch_bounds__(kSampleThreads) void sample_accept(SampleArgs a, int vec) {
+__global__ __launch_bounds__(kSampleThreads) void sample_accept(SampleArgs a) {
   __shared__ float lse_t[kMaxNodes];
   __shared__ float ef[kMaxNodes];        // effective mass of each node's token at its parent
   __shared__ int tokl[kMaxNodes];
@@ -494,7 +493,7 @@ __global__ __launch_bounds__(kSampleThreads) void sample_accept(SampleArgs a, in
   unsigned long long kres = 0ull, kp = 0ull;
   for (long long xg = x0 + 8ll * tid; xg < x1; xg += 8ll * kSampleThreads) {
     float pl[8];
-    if (vec && xg + 8 <= x1) {
+    if (xg + 8 <= x1) {
       load8<F32>(a.logits, prow + xg, pl);
     } else {
 #pragma unroll
@@ -560,13 +559,11 @@ __global__ __launch_bounds__(64) void sample_finish(SampleArgs a) {
 // ------------------------------------------------------------ launch
 
 template <bool F32>
-static hipError_t launch_sample_t(const SampleArgs& a, const SamplePlan& p, int vec,
-                                  hipStream_t st) {
-  hipLaunchKernelGGL((lse_scan<F32>), dim3(p.lse_grid), dim3(kLseScanThreads), 0, st, a, vec);
+static hipError_t launch_sample_t(const SampleArgs& a, const SamplePlan& p, hipStream_t st) {
+  hipLaunchKernelGGL((lse_scan<F32>), dim3(p.lse_grid), dim3(kLseScanThreads), 0, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((sample_accept<F32>), dim3(a.B * p.nrace), dim3(kSampleThreads), 0, st, a,
-                     vec);
+  hipLaunchKernelGGL((sample_accept<F32>), dim3(a.B * p.nrace), dim3(kSampleThreads), 0, st, a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(sample_finish, dim3(a.B), dim3(64), 0, st, a);
@@ -578,7 +575,6 @@ hipError_t launch_sample(const void* logits, int f32, const int32_t* draft,
                          float temperature, int B, int N, int V, int Dmax, int32_t* accept_len,
                          int32_t* path, int32_t* corr, void* ws, hipStream_t st) {
   const SamplePlan p = sample_plan(B, N, V);
-  const int vec = (uintptr_t)logits % 16 == 0 && V % 8 == 0;
   SampleArgs a;
   a.logits = logits;
   a.draft = draft;
@@ -600,7 +596,7 @@ hipError_t launch_sample(const void* logits, int f32, const int32_t* draft,
   a.nrace = p.nrace;
   a.eps = p.eps;
   a.rps = p.rps;
-  return f32 ? launch_sample_t<true>(a, p, vec, st) : launch_sample_t<false>(a, p, vec, st);
+  return f32 ? launch_sample_t<true>(a, p, st) : launch_sample_t<false>(a, p, st);
 }
 
 }  // namespace tv
