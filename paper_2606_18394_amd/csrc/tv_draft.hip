@@ -13,15 +13,11 @@
 //   argmax.  Finish: one wave per row merges the splits.
 //
 // build: best-first expansion under a node budget, one wave per sequence.
-//   Node i is owned by lane i % 64 (slot i / 64), which keeps the score
-//   keys of its open nodes in registers and caches its best one; a pop is a
-//   wave maximum of those keys (an order-preserving unsigned image of the
-//   fp32 score) with ties settled by the lower node index, the owner
-//   rescans its slots in registers, and the up to W children go to W
-//   consecutive lanes.  The loop only logs the popped nodes; parents,
-//   tokens, depths and scores are rebuilt from that log at the end.  Scores
-//   are fp32 sums parent + log-probability, the comparisons that decide the
-//   tree.
+//   A pop is a wave maximum over the open nodes that can come next, held in
+//   registers, with ties settled by the lower node index.  The loop only
+//   logs the popped nodes; parents, tokens, depths and scores are rebuilt
+//   from that log at the end.  Scores are fp32 sums parent +
+//   log-probability, the comparisons that decide the tree.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -141,10 +137,10 @@ __device__ __forceinline__ void wave_best(float& v, int& i) {
 // sum that cancels to zero rounds to +0.0.)  Key 0 marks "no open node".
 __device__ __forceinline__ unsigned score_key(float s) {
   const unsigned u = __float_as_uint(s);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  return u ^ ((unsigned)((int)u >> 31) | 0x80000000u);
 }
 __device__ __forceinline__ float key_score(unsigned k) {
-  return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
+  return __uint_as_float(k ^ ((unsigned)((int)~k >> 31) | 0x80000000u));
 }
 
 // Wave-wide minimum of an unsigned value (the maximum, wave_max_u32, is in
@@ -159,6 +155,19 @@ __device__ __forceinline__ unsigned wave_min_u32(unsigned x) {
   const unsigned r0 = __builtin_amdgcn_readlane(x, 0), r1 = __builtin_amdgcn_readlane(x, 16);
   const unsigned r2 = __builtin_amdgcn_readlane(x, 32), r3 = __builtin_amdgcn_readlane(x, 48);
   return min(min(r0, r1), min(r2, r3));
+}
+
+// wave_max_u32 (tv_walk.h) on floats that are no NaN
+__device__ __forceinline__ float wave_max_f32(float v) {
+  unsigned x = __float_as_uint(v);
+  auto mx = [](unsigned p, unsigned q) { return __float_as_uint(fmaxf(__uint_as_float(p), __uint_as_float(q))); };
+  x = mx(x, dpp_u32<0xB1>(x));
+  x = mx(x, dpp_u32<0x4E>(x));
+  x = mx(x, dpp_u32<0x141>(x));
+  x = mx(x, dpp_u32<0x140>(x));
+  x = mx(x, dpp_bcast_u32<0x142, 0xA>(x));
+  x = mx(x, dpp_bcast_u32<0x143, 0xC>(x));
+  return __int_as_float(__builtin_amdgcn_readlane((int)x, 63));
 }
 
 // (m, s) with s = sum exp(x - m): merge of two such states
@@ -517,35 +526,151 @@ struct BuildArgs {
 };
 
 // Best-first expansion for budgets of at most 64 S nodes, one wave per
-// sequence.  Node i belongs to lane i % 64, slot i / 64.  A lane keeps, per
-// slot, the score key of its node while that node is open (0 otherwise)
-// and the slot and depth packed as slot << 8 | depth, plus its best open
-// node (largest key, lowest slot on equal keys).  A pop:
+// sequence.  Every pop but the last adds exactly W children, so node c >= 1 is
+// child (c - 1) % W of the ((c - 1) / W)-th popped node: both loops below only
+// log the popped nodes (index, depth, key) in LDS, and parents, tokens, depths
+// and scores are rebuilt from that log at the end, with the same fp32 sum the
+// loop's key came from.
+//
+// A pop is a chain of dependent instructions of one wave with nothing to hide
+// them, so what counts is the length of that chain: the number of pops is
+// fixed.  Two loops:
+//
+// pop_lists, for candidates in decreasing order at every depth (as draft_topw
+// gives them), none beyond kListLogp in size, and at most 512 pops.  The
+// children of one popped node then score in index order (fp32 addition is
+// monotone, and equal scores go by index), so of every child list only the
+// first node not yet popped can be the next pop.  List p (of the p-th popped
+// node) belongs to lane p % 64, slot p / 64: as many slots as pops / 64, where
+// the nodes would need W times as many.  A lane keeps per list the score of
+// the head, of the sibling behind it and of the head's own first child, so
+// that a pop only moves scores: the popped head's list takes its next one, and
+// the new list's head is the popped node's first child.  The terms of the
+// sums behind those are read from LDS once the owner is known and used only
+// after the next pop's wave maximum, which hides their latency.  -inf stands
+// for "no open node": it ends every row of the table of terms (a node's last
+// sibling, the children of the deepest nodes), and a sum with it stays -inf.
+//   About 85 instructions and 0.25 us a pop at one slot per lane.  Four trees,
+//   16 depths, against pop_nodes: budget 512 at W = 8 / 4 / 2 32.4 / 61.4 /
+//   120 -> 17.3 / 37.8 / 90 us, 2048 at W = 8 / 4 310 / 612 -> 94 / 266 us, 64
+//   at W = 4 5.7 -> 5.2 us.  Above 512 pops (W <= 3) its 16 slots would cost
+//   what pop_nodes' 32 do.  A first form with integer keys and branches for
+//   the two changed lists took 31 us at budget 512, W = 8.
+//
+// pop_nodes, for any candidates: node i belongs to lane i % 64, slot i / 64,
+// and a lane keeps per slot the score key of its node while that node is open
+// (0 otherwise) and the slot and depth packed as slot << 8 | depth, plus its
+// best open node (largest key, lowest slot on equal keys).  A pop:
 //  * the wave maximum of the lanes' best keys; the lanes holding it are a
 //    ballot, and with several (equal scores) the lowest node index wins;
 //  * the owner closes the node and rescans its slots in registers;
 //  * the up to W children go to consecutive lanes: child k of a depth-d
 //    node gets key(score + logp[d, k]) if depth d + 1 is below Nd, else 0.
-// Every pop but the last adds exactly W children, so node c >= 1 is child
-// (c - 1) % W of the ((c - 1) / W)-th popped node: the loop only logs the
-// popped nodes (index, depth, key) in LDS, and parents, tokens, depths
-// and scores are rebuilt from that log at the end, with the same fp32 sum
-// the loop's key came from.
-template <int S>
-__global__ __launch_bounds__(64) void build_tree(BuildArgs a) {
-  static_assert(S >= 1 && S <= kMaxNodes / 64, "slots per lane");
-  __shared__ float cand_lp[kMaxDraftDepth * kTopwMax];
-  __shared__ int cand_tok[kMaxDraftDepth * kTopwMax];
-  __shared__ unsigned pop_key[kMaxNodes];
-  __shared__ int pop_node[kMaxNodes];  // node index | depth << 16
-  const int b = blockIdx.x, lane = threadIdx.x;
-  const int Nd = a.Nd, W = a.W, budget = a.budget;
-  const size_t cbase = (size_t)b * Nd * W;
-  for (int k = lane; k < Nd * W; k += 64) {
-    cand_lp[k] = a.logp[cbase + k];
-    cand_tok[k] = a.tok[cbase + k];
+struct PopLog {
+  unsigned* key;
+  int* node;  // node index | depth << 16
+};
+
+constexpr int kMaxListSlots = 8;  // pop_lists: at most 64 * 8 pops
+
+// A list's state word: its number, the head's place k in it and the byte
+// offset of the table row of the head's children.  Words compare like the
+// heads' node indices (1 + W * number + k).
+constexpr int kWordList = 18, kWordK = 13, kWordRow = (1 << kWordK) - 1;
+constexpr int kListRow = kTopwMax + 2;  // a row: W terms, then -inf twice
+constexpr int kListTable = (kMaxDraftDepth + 1) * kListRow;
+constexpr float kListLogp = 1e36f;  // 64 of them add up to a finite score
+static_assert(4 * kListTable <= kWordRow && kTopwMax < (1 << (kWordList - kWordK)), "word fields");
+
+// Both loops return the number of nodes built.  This one has selects and no
+// divergent branches, which cost more than the work they would skip.  terms:
+// row r holds logp of the children of a node at depth r, rows W + 2 apart.
+template <int SL>
+__device__ __forceinline__ int pop_lists(const float* terms, PopLog log, int W, int budget, int lane) {
+  const int row = 4 * (W + 2);  // bytes
+  const int pops = (budget - 2 + W) / W;
+  float hk[SL], nx[SL], ck[SL];  // scores: head, the sibling behind it, the head's first child
+  float ps[SL];                  // and of the list's own node
+  unsigned hw[SL], pw[SL];       // words: the head's, and that of the list's own node
+#pragma unroll
+  for (int j = 0; j < SL; ++j) {
+    hk[j] = nx[j] = ck[j] = -INFINITY;
+    ps[j] = 0.f;
+    hw[j] = 0xFFFFFFFFu;
+    pw[j] = 0u;
   }
-  __syncthreads();
+  auto term = [&](int byte) { return *reinterpret_cast<const float*>((const char*)terms + byte); };
+  // Pop 0, the root, makes list 0.  Each pop leaves to the next one the
+  // number of the list whose head it took (olist) and the terms of four sums:
+  // of that list's sibling and first child, and of the new list's.
+  hk[0] = lane == 0 ? 0.f + term(0) : -INFINITY;  // (the sum: -0.0 becomes +0.0)
+  hw[0] = lane == 0 ? (unsigned)row : hw[0];
+  int olist = -1, p = 1;
+  float l_sib = 0.f, l_child = 0.f, l_sib2 = term(4), l_child2 = term(row);
+  for (; p < pops; ++p) {
+    float bk = hk[0];
+#pragma unroll
+    for (int j = 1; j < SL; ++j) bk = fmaxf(bk, hk[j]);
+    unsigned bw = hw[SL - 1];  // the lane's lowest list with the largest score
+#pragma unroll
+    for (int j = SL - 2; j >= 0; --j) bw = hk[j] == bk ? hw[j] : bw;
+    float g = wave_max_f32(bk);
+    // (keeps the wait for the terms behind the wave maximum)
+    asm volatile("" : "+s"(g), "+v"(l_sib), "+v"(l_child), "+v"(l_sib2), "+v"(l_child2));
+    if (g == -INFINITY) break;  // nothing open
+#pragma unroll
+    for (int j = 0; j < SL; ++j) {
+      const bool own = lane + 64 * j == olist, fresh = lane + 64 * j == p - 1;
+      const float s1 = ps[j] + (own ? l_sib : l_sib2), s2 = hk[j] + (own ? l_child : l_child2);
+      nx[j] = own || fresh ? s1 : nx[j];
+      ck[j] = own || fresh ? s2 : ck[j];
+    }
+    // the owner: equal scores go to the lowest node index
+    const unsigned long long hold = __ballot(bk == g);
+    int owner = __builtin_ctzll(hold);
+    if (__popcll(hold) != 1) {
+      const unsigned m = wave_min_u32(bk == g ? bw : 0xFFFFFFFFu);
+      owner = __builtin_ctzll(__ballot(bk == g && bw == m));
+    }
+    const unsigned w = (unsigned)__builtin_amdgcn_readlane((int)bw, owner);
+    olist = (int)(w >> kWordList);
+    // row r of the popped head's children; the head is in row r - 1, and the
+    // sibling behind its successor two places behind it
+    const int r = (int)(w & kWordRow);
+    l_sib = term(r - row + 4 * (int)((w >> kWordK) & ((1 << (kWordList - kWordK)) - 1)) + 8);
+    l_child = term(r);
+    l_sib2 = term(r + 4);
+    l_child2 = term(r + row);
+    float bc = ck[0];
+#pragma unroll
+    for (int j = 1; j < SL; ++j) bc = (olist >> 6) == j ? ck[j] : bc;
+    const float child = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bc), owner));
+#pragma unroll
+    for (int j = 0; j < SL; ++j) {
+      const bool own = lane + 64 * j == olist, fresh = lane + 64 * j == p;
+      hk[j] = own ? nx[j] : fresh ? child : hk[j];
+      hw[j] = own ? w + (1u << kWordK) : fresh ? (unsigned)p << kWordList | (unsigned)(r + row) : hw[j];
+      ps[j] = fresh ? g : ps[j];
+      pw[j] = fresh ? w : pw[j];
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < SL; ++j) {
+    const int l = lane + 64 * j;
+    if (l < p) {
+      const int k = (int)((pw[j] >> kWordK) & ((1 << (kWordList - kWordK)) - 1));
+      log.key[l] = score_key(ps[j]);
+      log.node[l] = l == 0 ? 0
+                           : (1 + W * (int)(pw[j] >> kWordList) + k) |
+                                 ((int)(pw[j] & kWordRow) / row) << 16;
+    }
+  }
+  return min(budget, 1 + W * p);
+}
+
+template <int S>
+__device__ __forceinline__ int pop_nodes(const float* cand_lp, PopLog log, int Nd, int W, int budget,
+                                         int lane) {
   unsigned key[S];
   int sd[S];
 #pragma unroll
@@ -605,12 +730,57 @@ __global__ __launch_bounds__(64) void build_tree(BuildArgs a) {
       bsd = csd;
     }
     if (lane == 0) {
-      pop_key[np] = g;
-      pop_node[np] = (jv * 64 + owner) | d << 16;
+      log.key[np] = g;
+      log.node[np] = (jv * 64 + owner) | d << 16;
     }
     ++np;
     n += nk;
   }
+  return n;
+}
+
+template <int S>
+__global__ __launch_bounds__(64) void build_tree(BuildArgs a) {
+  static_assert(S >= 1 && S <= kMaxNodes / 64, "slots per lane");
+  __shared__ float cand_lp[kMaxDraftDepth * kTopwMax];
+  __shared__ int cand_tok[kMaxDraftDepth * kTopwMax];
+  __shared__ float terms[kListTable];
+  __shared__ unsigned pop_key[kMaxNodes];
+  __shared__ int pop_node[kMaxNodes];
+  const int b = blockIdx.x, lane = threadIdx.x;
+  const int Nd = a.Nd, W = a.W, budget = a.budget;
+  const size_t cbase = (size_t)b * Nd * W;
+  for (int k = lane; k < Nd * W; k += 64) {
+    cand_lp[k] = a.logp[cbase + k];
+    cand_tok[k] = a.tok[cbase + k];
+  }
+  __syncthreads();
+  // the candidates suit pop_lists: every depth's in decreasing order, and
+  // scores that stay finite
+  bool other = false;
+  for (int k = lane; k < Nd * W; k += 64) {
+    other |= !(fabsf(cand_lp[k]) <= kListLogp);
+    if ((k + 1) % W != 0) other |= !(cand_lp[k] >= cand_lp[k + 1]);
+  }
+  // children at depth Nd are never open: row Nd - 1 holds -inf like row Nd
+  for (int k = lane; k < (Nd + 1) * (W + 2); k += 64) {
+    const int r = k / (W + 2), c = k % (W + 2);
+    terms[k] = r < Nd - 1 && c < W ? cand_lp[r * W + c] : -INFINITY;
+  }
+  __syncthreads();
+  const PopLog log{pop_key, pop_node};
+  const int pops = (budget - 2 + W) / W;
+  int n;
+  if (__any(other) || pops > 64 * kMaxListSlots)
+    n = pop_nodes<S>(cand_lp, log, Nd, W, budget, lane);
+  else if (pops <= 64)
+    n = pop_lists<1>(terms, log, W, budget, lane);
+  else if (pops <= 128)
+    n = pop_lists<2>(terms, log, W, budget, lane);
+  else if (pops <= 256)
+    n = pop_lists<4>(terms, log, W, budget, lane);
+  else
+    n = pop_lists<kMaxListSlots>(terms, log, W, budget, lane);
   __syncthreads();
   const size_t obase = (size_t)b * budget;
 #pragma unroll

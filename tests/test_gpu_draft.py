@@ -178,3 +178,25 @@ def test_workload_drafting(name):
     for b in range(w.B):
         assert n[b] == w.N and par[b, 0] == -1
         assert ((par[b, 1:] >= 0) & (par[b, 1:] < np.arange(1, w.N))).all()
+
+
+# decreasing candidates: pops on each side of 64, 128, 256 and 512 (the
+# builder keeps 1, 2, 4 or 8 child lists per lane, and above that nodes)
+LIST_CASES = [
+    (8, 513), (8, 514), (3, 193), (3, 195), (4, 512), (4, 514), (2, 512), (2, 514), (16, 2048),
+    (5, 1281), (5, 1282), (2, 1025), (2, 1026), (4, 2048), (1, 65), (1, 66), (1, 513), (1, 514),
+    (6, 2), (6, 1),
+]
+
+
+@pytest.mark.parametrize("kind", ["normal", "ties", "rising", "huge"])
+def test_build_list_slots(kind):
+    """Trees from decreasing candidates, also with positive log-probabilities
+    (a child above its parent) and sums that overflow."""
+    for W, budget in LIST_CASES:
+        rng = np.random.default_rng(1000 * W + budget)
+        B, Nd = 2, min(64, 10 if W > 1 else budget)
+        tok, lp = _candidates(rng, B, Nd, W, "mixed" if kind == "rising" else kind)
+        lp = -np.sort(-lp, axis=-1)
+        print(f"W={W} budget={budget} {kind}", flush=True)
+        _compare_trees(_gpu_build(tok, lp, budget), oracle.build_tree(tok, lp, budget))
