@@ -4,6 +4,7 @@
 // per-device cache of that array's address.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <string.h>
 
 #include <atomic>
 
@@ -39,6 +40,24 @@ hipError_t launch_build_tree(const int32_t* tok, const float* logp, const int32_
 }  // namespace tv
 
 static_assert(TV_MAX_WIDTH == tv::kTopwMax, "width limit mismatch");
+
+// The plan of a shape.  Serving calls come with the same shape over and over
+// and each needs its plan twice (workspace size, launch), so every thread keeps
+// the last one: the search over the arrangements takes about as long as a
+// launch.
+static const tv::AttnPlan& attn_plan_of(int B, int N, int Hq, int Hkv, int D, int Lmax) {
+  struct Last {
+    int key[6];
+    tv::AttnPlan plan;
+  };
+  static thread_local Last last = {};
+  const int key[6] = {B, N, Hq, Hkv, D, Lmax};
+  if (memcmp(key, last.key, sizeof key) != 0) {
+    last.plan = tv::attn_plan(B, N, Hq, Hkv, D, Lmax);
+    memcpy(last.key, key, sizeof key);
+  }
+  return last.plan;
+}
 
 static bool misaligned(const void* p) { return ((uintptr_t)p & 15u) != 0; }
 
@@ -114,7 +133,7 @@ int tv_version(void) { return 2; }
 
 size_t tv_tree_verify_attention_workspace(int B, int N, int Hq, int Hkv, int D, int Lmax) {
   if (check_attention_sizes(B, N, Hq, Hkv, D, Lmax) != TV_OK) return 0;
-  const tv::AttnPlan p = tv::attn_plan(B, N, Hq, Hkv, D, Lmax);
+  const tv::AttnPlan& p = attn_plan_of(B, N, Hq, Hkv, D, Lmax);
   return p.ws_bytes > 0 ? p.ws_bytes : 256;
 }
 
@@ -131,7 +150,7 @@ int tv_tree_verify_attention(const void* q, const void* k_cache, const void* v_c
   if (misaligned(q) || misaligned(out) ||
       (Lmax > 0 && (misaligned(k_cache) || misaligned(v_cache))))
     return TV_ERR_ALIGN;
-  const tv::AttnPlan p = tv::attn_plan(B, N, Hq, Hkv, D, Lmax);
+  const tv::AttnPlan& p = attn_plan_of(B, N, Hq, Hkv, D, Lmax);
   if (p.ws_bytes > 0 && (!workspace || workspace_bytes < p.ws_bytes)) return TV_ERR_WORKSPACE;
   if (misaligned(workspace)) return TV_ERR_ALIGN;
   if (!(scale > 0.f)) scale = 1.0f / sqrtf((float)D);
@@ -144,7 +163,7 @@ int tv_tree_verify_attention(const void* q, const void* k_cache, const void* v_c
 size_t tv_block_causal_attention_workspace(int B, int A, int S, int Hq, int Hkv, int D,
                                           int L) {
   if (check_block_causal(B, A, S, Hq, Hkv, D, L) != TV_OK) return 0;
-  const tv::AttnPlan p = tv::attn_plan(B * A, S, Hq, Hkv, D, L);
+  const tv::AttnPlan& p = attn_plan_of(B * A, S, Hq, Hkv, D, L);
   return p.ws_bytes > 0 ? p.ws_bytes : 256;
 }
 
@@ -160,7 +179,7 @@ int tv_block_causal_attention(const void* q, const void* k_ctx, const void* v_ct
   if (misaligned(q) || misaligned(k_blk) || misaligned(v_blk) || misaligned(out) ||
       (L > 0 && (misaligned(k_ctx) || misaligned(v_ctx))))
     return TV_ERR_ALIGN;
-  const tv::AttnPlan p = tv::attn_plan(B * A, S, Hq, Hkv, D, L);
+  const tv::AttnPlan& p = attn_plan_of(B * A, S, Hq, Hkv, D, L);
   if (p.ws_bytes > 0 && (!workspace || workspace_bytes < p.ws_bytes)) return TV_ERR_WORKSPACE;
   if (misaligned(workspace)) return TV_ERR_ALIGN;
   if (!(scale > 0.f)) scale = 1.0f / sqrtf((float)D);
@@ -189,7 +208,7 @@ int tv_tree_verify_attention_paged(const void* q, const void* k_pool, const void
   if (misaligned(q) || misaligned(out) ||
       (Lmax > 0 && (misaligned(k_pool) || misaligned(v_pool))))
     return TV_ERR_ALIGN;
-  const tv::AttnPlan p = tv::attn_plan(B, N, Hq, Hkv, D, Lmax);
+  const tv::AttnPlan& p = attn_plan_of(B, N, Hq, Hkv, D, Lmax);
   if (p.ws_bytes > 0 && (!workspace || workspace_bytes < p.ws_bytes)) return TV_ERR_WORKSPACE;
   if (misaligned(workspace)) return TV_ERR_ALIGN;
   if (!(scale > 0.f)) scale = 1.0f / sqrtf((float)D);

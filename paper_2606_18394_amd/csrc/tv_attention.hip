@@ -41,7 +41,11 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <atomic>
+#include <mutex>
+
 #include "tv_plan.h"
+#include "tv_walk.h"
 
 namespace tv {
 
@@ -66,6 +70,7 @@ struct AttnArgs {
   int* tree_bad;          // per row block: invalid parent array seen
   int B, N, Hq, Hkv, Lmax, G, M, nRB, S, chunk, nwork;
   int fused;   // split-KV merge inside the main kernel (else a second kernel)
+  int slots, min_chunk;  // even split (tv_plan.h): chunks per (KV head, row block), else 0
   int spread;  // work order of several sequences (tv_plan.h, work_item)
   float c;  // scale * log2(e): scores live in base-2 exponent units
   const int32_t* block_table;  // paged cache: [B, max_blocks], else NULL
@@ -154,6 +159,72 @@ __device__ __forceinline__ void longest_first(const AttnArgs& a, int bid, WorkIt
   }
   it.b = p / per_b;
   it.s = ((ln - it.b) % L + L) % L + L * (p % per_b);
+}
+
+// Tiles of sequence b for its last row block (the chunk sizes must not depend
+// on the row block: a chunk's row blocks read the same keys).
+__device__ __forceinline__ int sequence_tiles(const AttnArgs& a, int b) {
+  const int cap = a.tail ? a.Lmax - a.N : a.Lmax;
+  int kvl = a.kv_len ? a.kv_len[b] : cap;
+  kvl = kvl < 0 ? 0 : (kvl > cap ? cap : kvl);
+  return a.tail ? (kvl + a.N + kKeyTile - 1) / kKeyTile
+                : (kvl + kKeyTile - 1) / kKeyTile + (a.N - 1) / kKeyTile + 1;
+}
+
+__device__ __forceinline__ int wave_sum(int x) {
+  x += (int)dpp_u32<0xB1>((unsigned)x);
+  x += (int)dpp_u32<0x4E>((unsigned)x);
+  x += (int)dpp_u32<0x141>((unsigned)x);
+  x += (int)dpp_u32<0x140>((unsigned)x);
+  return __builtin_amdgcn_readlane(x, 0) + __builtin_amdgcn_readlane(x, 16) +
+         __builtin_amdgcn_readlane(x, 32) + __builtin_amdgcn_readlane(x, 48);
+}
+
+// ceil(x / c) for 1 <= x, c < 2^20: the quotient's distance to the next whole
+// number below, at least 1 / (2 c), is far above the reciprocal's error
+__device__ __forceinline__ int ceil_div(int x, int c, float rc) {
+  return (int)(((float)(x + c) - 0.5f) * rc);
+}
+
+// Even split of the batch (a.slots > 0): one chunk size for all sequences,
+// the smallest for which they need at most a.slots chunks together.  Found
+// from the kv_lens by every wave alike (one sequence per lane, bisection on
+// the chunk size with wave-wide sums), in a few hundred cycles; B = 1 needs
+// one division.  `first` is the lane's sequence's first chunk in the order of
+// the sequences and `count` the number of chunks in all.
+struct EvenSplit {
+  int chunk, first, count;
+};
+__device__ __forceinline__ EvenSplit even_split(const AttnArgs& a) {
+  const int lane = threadIdx.x & 63;
+  if (a.B == 1) {
+    const int t = sequence_tiles(a, 0);
+    const int chunk = max(a.min_chunk, (t + a.slots - 1) / a.slots);
+    return EvenSplit{chunk, 0, (t + chunk - 1) / chunk};
+  }
+  const int t = lane < a.B ? sequence_tiles(a, lane) : 0;
+  const int total = wave_sum(t), longest = (int)wave_max_u32((unsigned)t);
+  // below lo the chunks are too small or too many; at hi they are few enough:
+  // the sum of ceil(t / hi) is below total / hi + B
+  int lo = max(a.min_chunk, (total + a.slots - 1) / a.slots) - 1;
+  int hi = a.slots > a.B ? min(longest, (total + a.slots - a.B - 1) / (a.slots - a.B)) : longest;
+  hi = max(hi, lo + 1);
+  auto chunks = [&](int c) {
+    return lane < a.B ? ceil_div(t, c, __builtin_amdgcn_rcpf((float)c)) : 0;
+  };
+  while (hi - lo > 1) {
+    const int mid = lo + ((hi - lo) >> 1);
+    if (wave_sum(chunks(mid)) <= a.slots) hi = mid;
+    else lo = mid;
+  }
+  const int n = chunks(hi);
+  int incl = n;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(incl, o);
+    if (lane >= o) incl += y;
+  }
+  return EvenSplit{hi, incl - n, __builtin_amdgcn_readlane(incl, 63)};
 }
 
 // Four output values, or four NaN when the sequence's tree is invalid (the
@@ -266,21 +337,14 @@ __device__ __forceinline__ void wait_vm_any(int n) {
   }
 }
 
-// n is (tiles still in flight) x (DMAs per tile); only these values occur
-__device__ __forceinline__ void wait_vm_dyn(int n) {
-  switch (n) {
-    case 1: wait_vm<1>(); break;
-    case 2: wait_vm<2>(); break;
-    case 3: wait_vm<3>(); break;
-    case 4: wait_vm<4>(); break;
-    case 6: wait_vm<6>(); break;
-    case 8: wait_vm<8>(); break;
-    case 12: wait_vm<12>(); break;
-    case 16: wait_vm<16>(); break;
-    case 24: wait_vm<24>(); break;
-    case 32: wait_vm<32>(); break;
-    case 48: wait_vm<48>(); break;
-    default: wait_vm<0>(); break;
+// s_waitcnt vmcnt(PW * min(n, T)): at most n tiles of PW DMAs in flight
+template <int PW, int T>
+__device__ __forceinline__ void wait_tiles(int n) {
+  if constexpr (T == 0) {
+    wait_vm<0>();
+  } else {
+    if (n >= T) wait_vm<T * PW>();
+    else wait_tiles<PW, T - 1>(n);
   }
 }
 
@@ -392,29 +456,48 @@ constexpr float kSlack = 8.f;  // log2 units a row's reference may lag its maxim
 
 // Steps of one 32-key tile for a wave's 32 rows (two 16-row tiles nt).
 //
+// The compiler must not move instructions across this point: it would sink
+// the LDS reads to just before their uses (fewer registers) and chain the
+// score products, and the tile then waits for every LDS and matrix latency in
+// turn.
+__device__ __forceinline__ void pin_order() { __builtin_amdgcn_sched_barrier(0); }
+
+// The tile's V^T operand from transposing LDS reads: lane (g4, l16) receives
+// V[key 4*g4 + j (+16)][16*dt + l16], the key order of P^T.
+template <int D>
+__device__ __forceinline__ void read_values(const unsigned char* vt_lds, i16x4 (&vf)[D / 16][2],
+                                            int g4, int l16) {
+  using TL = TileLayout<D>;
+#pragma unroll
+  for (int dt = 0; dt < D / 16; ++dt) {
+    const int rr = 4 * g4 + (l16 >> 2);
+    const int chunk = 2 * dt + ((l16 & 3) >> 1);
+    const int inb = 8 * (l16 & 1);
+    vf[dt][0] =
+        __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(vt_lds + TL::off(rr, chunk) + inb));
+    vf[dt][1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+        (lds_i16x4*)(vt_lds + TL::off(rr + 16, chunk) + inb));
+  }
+}
+
 // scores: S^T = K Q^T on the matrix cores; lane (g4, l16) holds
 //   S^T[key 16*tt + 4*g4 + j][row 16*nt + l16].
 template <int D, int NT>
-__device__ __forceinline__ void tile_scores(const unsigned char* kt_lds, const bf16x8 (&qf)[NT][D / 32],
-                                            f32x4 (&sc)[2][NT], int g4, int l16) {
-  using TL = TileLayout<D>;
+__device__ __forceinline__ void tile_scores(const bf16x8 (&kf)[2][D / 32], const bf16x8 (&qf)[NT][D / 32],
+                                            f32x4 (&sc)[2][NT]) {
   constexpr int NC = D / 32;
-  bf16x8 kf[2][NC];
 #pragma unroll
-  for (int tt = 0; tt < 2; ++tt)
+  for (int cc = 0; cc < NC; ++cc) {
 #pragma unroll
-    for (int cc = 0; cc < NC; ++cc)
-      kf[tt][cc] = *reinterpret_cast<const bf16x8*>(kt_lds + TL::off(16 * tt + l16, 4 * cc + g4));
+    for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-    for (int tt = 0; tt < 2; ++tt) {
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int cc = 0; cc < NC; ++cc)
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[tt][cc], qf[nt][cc], acc, 0, 0, 0);
-      sc[tt][nt] = acc;
-    }
+      for (int nt = 0; nt < NT; ++nt) {
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+        sc[tt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[tt][cc], qf[nt][cc],
+                                                             cc == 0 ? zero : sc[tt][nt], 0, 0, 0);
+      }
+    pin_order();
+  }
 }
 
 // mask: -inf for cache keys at or past kv_len and for tree keys outside
@@ -518,30 +601,21 @@ __device__ __forceinline__ void tile_weights(const f32x4 (&sc)[2][NT], const flo
 }
 
 // values: row sums ones^T P^T into lacc (same rounded weights as the
-//   numerator) and O^T += V^T P^T with V^T from transposing LDS reads: lane
-//   (g4, l16) receives V[key 4*g4 + j (+16)][16*dt + l16], the key order of P^T.
+//   numerator) and O^T += V^T P^T.
 template <int D, int NT>
-__device__ __forceinline__ void tile_values(const unsigned char* vt_lds, const bf16x8 (&pf)[NT],
+__device__ __forceinline__ void tile_values(const i16x4 (&vf)[D / 16][2], const bf16x8 (&pf)[NT],
                                             const bf16x8& ones, f32x4 (&o)[D / 16][NT],
-                                            f32x4 (&lacc)[NT], int g4, int l16) {
-  using TL = TileLayout<D>;
+                                            f32x4 (&lacc)[NT]) {
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt)
     lacc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[nt], lacc[nt], 0, 0, 0);
 #pragma unroll
   for (int dt = 0; dt < D / 16; ++dt) {
-    const int rr = 4 * g4 + (l16 >> 2);
-    const int chunk = 2 * dt + ((l16 & 3) >> 1);
-    const int inb = 8 * (l16 & 1);
-    const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (lds_i16x4*)(vt_lds + TL::off(rr, chunk) + inb));
-    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (lds_i16x4*)(vt_lds + TL::off(rr + 16, chunk) + inb));
-    const bf16x4 lob = __builtin_bit_cast(bf16x4, lo), hib = __builtin_bit_cast(bf16x4, hi);
-    const bf16x8 vf = {lob[0], lob[1], lob[2], lob[3], hib[0], hib[1], hib[2], hib[3]};
+    const bf16x4 lo = __builtin_bit_cast(bf16x4, vf[dt][0]), hi = __builtin_bit_cast(bf16x4, vf[dt][1]);
+    const bf16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
-      o[dt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[nt], o[dt][nt], 0, 0, 0);
+      o[dt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, pf[nt], o[dt][nt], 0, 0, 0);
   }
 }
 
@@ -552,19 +626,33 @@ __device__ __forceinline__ void attend_tile(const unsigned char* kt_lds, const b
                                             float (&m)[NT], float (&thr)[NT], const bf16x8& ones,
                                             float c, float inv_c, const MaskInfo& mk,
                                             const int (&node_rel)[NT], int g4, int l16) {
+  using TL = TileLayout<D>;
+  constexpr int NC = D / 32;
+  // All of the tile's LDS reads go out first, K before V.
+  bf16x8 kf[2][NC];
+#pragma unroll
+  for (int cc = 0; cc < NC; ++cc)
+#pragma unroll
+    for (int tt = 0; tt < 2; ++tt)
+      kf[tt][cc] = *reinterpret_cast<const bf16x8*>(kt_lds + TL::off(16 * tt + l16, 4 * cc + g4));
+  i16x4 vf[D / 16][2];
+  pin_order();
   f32x4 sc[2][NT];
   // The score products run at raised wave priority: the SIMD's other wave
   // is then mostly in its softmax (vector work) while these matrix
   // instructions issue back to back (measured 5-8% faster on matrix-bound
   // shapes than equal priority or raising it for the value products too).
   __builtin_amdgcn_s_setprio(1);
-  tile_scores<D, NT>(kt_lds, qf, sc, g4, l16);
+  tile_scores<D, NT>(kf, qf, sc);
   __builtin_amdgcn_s_setprio(0);
+  read_values<D>(kt_lds + TL::kBytes, vf, g4, l16);
+  pin_order();
   if (kMasked) tile_mask<NT>(sc, mk, node_rel);
   tile_reference<D / 16, NT>(sc, m, thr, o, lacc, c, inv_c);
   bf16x8 pf[NT];
   tile_weights<NT>(sc, m, c, pf);
-  tile_values<D, NT>(kt_lds + TileLayout<D>::kBytes, pf, ones, o, lacc, g4, l16);
+  pin_order();
+  tile_values<D, NT>(vf, pf, ones, o, lacc);
 }
 
 // Merge of the chunk partials of one row block, run by the workgroup whose
@@ -589,6 +677,7 @@ __device__ __forceinline__ void merge_chunks(const AttnArgs& a, size_t part0, in
 #pragma unroll
   for (int k = 0; k < NPW; ++k) {
     const int ntg = kSplitCols ? wave % NTG : wave + k * kWaves;
+    if (r0 + ntg * 16 >= a.M) continue;  // no rows
     const int dt0 = kSplitCols ? wave / NTG : 0;
     const int row = ntg * 16 + l16;
     float m = -INFINITY, l = 0.f;
@@ -660,8 +749,21 @@ void attn_main(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
   WorkItem it{};
-  if (!work_item(gridDim.x, a.nwork, a.S, a.nRB, a.spread, a.B, a.Hkv, blockIdx.x, it)) return;
-  if (a.spread == 2) longest_first(a, blockIdx.x, it);
+  int chunk = a.chunk, part0;  // part0: the row block's first chunk partial
+  if (a.slots > 0) {
+    const EvenSplit ev = even_split(a);
+    chunk = ev.chunk;
+    const int item = even_item(blockIdx.x, ev.count, a.nRB, a.Hkv, it);
+    if (item < 0) return;
+    // the last sequence that starts at or before the item
+    it.b = a.B == 1 ? 0 : __popcll(__ballot((int)(threadIdx.x & 63) < a.B && ev.first <= item)) - 1;
+    it.s = item - (a.B == 1 ? 0 : __builtin_amdgcn_readlane(ev.first, it.b));
+    part0 = (it.g * a.nRB + it.rb) * a.slots + item - it.s;
+  } else {
+    if (!work_item(gridDim.x, a.nwork, a.S, a.nRB, a.spread, a.B, a.Hkv, blockIdx.x, it)) return;
+    if (a.spread == 2) longest_first(a, blockIdx.x, it);
+    part0 = ((it.b * a.Hkv + it.g) * a.nRB + it.rb) * a.S;
+  }
   const int s = it.s, rb = it.rb, g = it.g, b = it.b;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -674,8 +776,8 @@ void attn_main(AttnArgs a) {
   const Segment sg = segment(a, b, i_hi);
   const int kvl = sg.kvl, nct = sg.nct, T = sg.T;
   const int ntt = i_hi / kKeyTile + 1;  // words of a node's ancestor bitmask
-  const int t0 = s * a.chunk;
-  const int t1 = min(T, t0 + a.chunk);
+  const int t0 = s * chunk;
+  const int t1 = min(T, t0 + chunk);
   if (t0 >= t1) return;  // empty chunk: the merge reads only chunks with tiles
   const bool has_tree = a.tail ? t1 * kKeyTile > kvl : t1 > nct;
 
@@ -867,7 +969,10 @@ void attn_main(AttnArgs a) {
   auto ring_step = [&](int i) {
     const bool mine = i < n_mine;
     if (WR > 1) {
-      if (mine) wait_vm_dyn(min(n_mine - 1 - i, i == 0 ? NS - 1 : NS - 2) * PW);
+      if (mine) {
+        if (i == 0) wait_tiles<PW, NS - 1>(n_mine - 1);
+        else wait_tiles<PW, NS - 2>(n_mine - 1 - i);
+      }
       __syncthreads();
       if (i >= 1 && i + NS - 1 < n_mine)
         issue_tile<D, PW, kPaged>(src, dma_off, wr, lane, t0 + wk + WK * (i + NS - 1),
@@ -876,7 +981,7 @@ void attn_main(AttnArgs a) {
       if (i + NS - 1 < n_mine)
         issue_tile<D, PW, kPaged>(src, dma_off, wr, lane, t0 + wk + WK * (i + NS - 1),
                           ring + ((i + NS - 1) % NS) * STAGE);
-      if (mine) wait_vm_dyn(min(n_mine - 1 - i, NS - 1) * PW);
+      if (mine) wait_tiles<PW, NS - 1>(n_mine - 1 - i);
     }
   };
   // Full cache tiles first, without masking; the tiles that need a mask
@@ -890,19 +995,22 @@ void attn_main(AttnArgs a) {
       for (int c = 0; c < NC; ++c)
         qf[nt][c] = *reinterpret_cast<const bf16x8*>(qt + TL::off(16 * nt + l16, 4 * c + g4));
   };
+  // a wave whose rows all lie past the last one only moves tiles
+  const bool busy = wrow0 < a.M;
   int i = 0;
   for (; i < n_iter; ++i) {
     ring_step(i);
     if (i == 0 && qshare && wk != 0) shared_queries();
     const int t = t0 + wk + WK * i;
     if (i >= n_mine || t >= nct || (t + 1) * kKeyTile > kvl) break;
+    if (!busy) continue;
     const MaskInfo mk{t, nct, kvl, ntt, g4, a.tail, anc};
     attend_tile<D, NT, false>(ring_ptr + (i % NS) * STAGE, qf, o, lacc, m, thr, ones_v, a.c, inv_c,
                               mk, node_rel, g4, l16);
   }
   for (bool stepped = true; i < n_iter; ++i, stepped = false) {
     if (!stepped) ring_step(i);
-    if (i >= n_mine) continue;
+    if (i >= n_mine || !busy) continue;
     const int t = t0 + wk + WK * i;
     const MaskInfo mk{t, nct, kvl, ntt, g4, a.tail, anc};
     attend_tile<D, NT, true>(ring_ptr + (i % NS) * STAGE, qf, o, lacc, m, thr, ones_v, a.c, inv_c,
@@ -913,15 +1021,18 @@ void attn_main(AttnArgs a) {
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) lsum[nt] = lacc[nt][0];
   const int invalid = has_tree ? *flag : 0;
+  // Only chunks that hold tiles take part in a merge, nval of them; a row
+  // block that is one chunk needs none and writes its output here.
+  const int nval = (T + chunk - 1) / chunk;
+  const bool whole = a.S == 1 || nval == 1;
   const int bg = b * a.Hkv + g;
   const size_t grp = (size_t)bg * a.nRB + rb;  // row block id
-  const size_t part0 = grp * a.S;              // its first chunk partial
 
   // Final values of one 16x16 fragment (dt, ntg) of this workgroup's rows:
   // either the normalised bf16 output (single chunk) or the chunk partial.
   auto emit = [&](int dt, int ntg, const f32x4& acc, float mstar, float l) {
     const int row = ntg * 16 + l16;
-    if (a.S == 1) {
+    if (whole) {
       const int r = r0 + row;
       if (r < a.M) {
         const int node = r / a.G, h = g * a.G + r % a.G;
@@ -929,8 +1040,8 @@ void attn_main(AttnArgs a) {
                    1.f / l, invalid != 0);
       }
     } else {
-      f32x4* po = &a.ws_o[((part0 + s) * DT * NTG + dt * NTG + ntg) * 64 + lane];
-      float2* pml = &a.ws_ml[(part0 + s) * RB + row];
+      f32x4* po = &a.ws_o[((size_t)(part0 + s) * DT * NTG + dt * NTG + ntg) * 64 + lane];
+      float2* pml = &a.ws_ml[(size_t)(part0 + s) * RB + row];
       if (a.fused) {  // read by another workgroup of this kernel
         store_dev(po, acc);
         if (dt == 0 && g4 == 0) store_dev(pml, make_float2(mstar, l));
@@ -981,14 +1092,12 @@ void attn_main(AttnArgs a) {
       emit(dt, wr * NT + nt, acc, mstar, l);
     }
   }
-  if (a.S == 1 || !a.fused) return;
+  if (whole || !a.fused) return;
 
   // ---- fused split-KV merge: the chunk that arrives last merges its row
   // block.  Every workgroup publishes its partial (device-scope stores,
   // completed before the count), then counts itself in; the one that
   // completes the count merges and resets the counter for the next call.
-  // Only chunks that hold tiles take part: nval of them.
-  const int nval = min(a.S, (T + a.chunk - 1) / a.chunk);
   __shared__ int s_last;
   if (has_tree && tid == 0)  // every row block has a chunk with tree tiles
     __hip_atomic_store(a.tree_bad + grp, invalid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1039,17 +1148,31 @@ __global__ __launch_bounds__(256) void attn_combine(AttnArgs a) {
   // chunks of this row block that hold tiles (the same count the main
   // kernel derives from kv_len and the block's last node)
   const int i_hi = (min(rb * RB + RB, a.M) - 1) / a.G;
-  const size_t base = (size_t)(bg * a.nRB + rb) * a.S;  // first chunk partial
+  int chunk = a.chunk, nslot = a.S;
+  size_t base = (size_t)(bg * a.nRB + rb) * a.S;  // first chunk partial
+  if (a.slots > 0) {
+    nslot = a.slots;
+    base = (size_t)(g * a.nRB + rb) * a.slots;
+    if (a.B > 1) {
+      const EvenSplit ev = even_split(a);
+      chunk = ev.chunk;
+      const int first = __builtin_amdgcn_readlane(ev.first, b);
+      base += first;
+      nslot -= first;
+    }
+  }
   float2 ml0[U];
   f32x4 ov0[U];
 #pragma unroll
   for (int u = 0; u < U; ++u)
-    if (u < a.S) {
+    if (u < nslot) {
       ml0[u] = a.ws_ml[(base + u) * RB + row];
       ov0[u] = a.ws_o[((base + u) * DT * NTG + dt * NTG + ntg) * 64 + lane];
     }
   const int T = segment(a, b, i_hi).T;
-  const int nval = min(a.S, (T + a.chunk - 1) / a.chunk);
+  if (a.slots > 0 && a.B == 1) chunk = even_split(a).chunk;
+  const int nval = (T + chunk - 1) / chunk;
+  if (nval == 1) return;  // written by its only chunk
   float m = -INFINITY, l = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   for (int s0 = 0; s0 < nval; s0 += U) {
@@ -1099,10 +1222,25 @@ __global__ __launch_bounds__(256) void attn_combine(AttnArgs a) {
 
 template <int D, int WR, int WK, int NS, bool kPaged, bool kShareQ>
 static hipError_t launch_main(const AttnArgs& a, const AttnPlan& p, hipStream_t st) {
-  hipError_t e = hipFuncSetAttribute((const void*)attn_main<D, WR, WK, NS, kPaged, kShareQ>,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds_bytes);
+  // the kernel's LDS limit on each device, raised only when a call needs more
+  constexpr int kDevices = 64;
+  static std::atomic<int> limit[kDevices];
+  int dev = -1;
+  hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((attn_main<D, WR, WK, NS, kPaged, kShareQ>), dim3(p.grid), dim3(64 * WR * WK),
+  if (dev < 0 || dev >= kDevices) return hipErrorInvalidDevice;
+  if (limit[dev].load(std::memory_order_acquire) < (int)p.lds_bytes) {
+    static std::mutex raising;
+    std::lock_guard<std::mutex> hold(raising);
+    if (limit[dev].load(std::memory_order_relaxed) < (int)p.lds_bytes) {
+      e = hipFuncSetAttribute((const void*)attn_main<D, WR, WK, NS, kPaged, kShareQ>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds_bytes);
+      if (e != hipSuccess) return e;
+      limit[dev].store((int)p.lds_bytes, std::memory_order_release);
+    }
+  }
+  hipLaunchKernelGGL((attn_main<D, WR, WK, NS, kPaged, kShareQ>),
+                     dim3(p.slots > 0 ? p.even_grid : p.grid), dim3(64 * WR * WK),
                      p.lds_bytes, st, a);
   return hipGetLastError();
 }
@@ -1180,6 +1318,8 @@ hipError_t launch_attention(const void* q, const void* kc, const void* vc, const
   a.nwork = p.nwork;
   a.fused = p.fused;
   a.spread = p.spread;
+  a.slots = p.slots;
+  a.min_chunk = p.min_chunk;
   a.c = scale * 1.4426950408889634f;
   return D == 128 ? launch_attn_d<128>(a, p, st) : launch_attn_d<64>(a, p, st);
 }

@@ -29,8 +29,8 @@ constexpr int kRowsPerWave = 32;
 // leaves its counters at zero.  Plans with more row blocks do not split.
 constexpr int kSyncGroups = 4096;
 constexpr size_t kSyncBytes = (size_t)kSyncGroups * 8;
-constexpr int kFusedMergeBytes = 1024;
 constexpr int kWavesPerCU = 8;
+constexpr int kEvenSequences = 64;  // batches the even split takes (one per lane)
 constexpr size_t kMaxLds = 160 * 1024;
 
 struct Arrangement {
@@ -50,8 +50,9 @@ struct AttnPlan {
   int WR, WK, NS, threads, wg_per_cu;
   int G, M, RB, nRB, S, chunk;
   int nwork, grid;             // work items, launched workgroups (x8 padded)
-  int fused;                   // S > 1: merge in the main kernel's last chunk
+  int fused;                   // S > 1: merge in the main kernel's last chunk (else a second kernel)
   int spread;                  // work order of several sequences (below)
+  int slots, min_chunk, even_grid;  // even split (below), else slots = 0
   size_t ws_o_bytes, ws_ml_bytes, ws_sync_bytes, ws_bytes;
   size_t lds_bytes;            // dynamic LDS of the main kernel
   int qshare;                  // key group 0 loads the queries, the others read them from LDS
@@ -72,9 +73,9 @@ inline size_t attn_lds_bytes(int D, int WR, int WK, int NS, int G, int N, bool q
   return a > merge ? a : merge;
 }
 
-// The plan for one arrangement: split count and sizes (grid sized to fill
-// every CU with its workgroups-per-CU).
-inline AttnPlan attn_plan_arr(int B, int N, int Hq, int Hkv, int D, int Lmax, int arr) {
+// The plan for one arrangement and `want` chunks per (KV head, row block) over
+// all sequences (at least B; B: no split).
+inline AttnPlan attn_plan_arr(int B, int N, int Hq, int Hkv, int D, int Lmax, int arr, long long want) {
   const Arrangement& ar = kArrangements[arr];
   AttnPlan p{};
   p.arr = arr;
@@ -82,26 +83,28 @@ inline AttnPlan attn_plan_arr(int B, int N, int Hq, int Hkv, int D, int Lmax, in
   p.WK = ar.WK;
   p.NS = arr_stages(ar, D);
   p.threads = 64 * ar.WR * ar.WK;
-  p.wg_per_cu = kWavesPerCU / (ar.WR * ar.WK);
   p.G = Hq / Hkv;
+  p.wg_per_cu = kWavesPerCU / (ar.WR * ar.WK);
+  p.lds_bytes = p.NS > 0 ? attn_lds_bytes(D, ar.WR, ar.WK, p.NS, p.G, N, false) : kMaxLds + 1;
   p.M = N * p.G;
   p.RB = kRowsPerWave * ar.WR;
   p.nRB = cdiv(p.M, p.RB);
   const int tiles = cdiv(Lmax, kKeyTile) + cdiv(N, kKeyTile);
   const long long base = (long long)B * Hkv * p.nRB;
-  const long long target = 256LL * p.wg_per_cu;  // every CU full
-  const int min_chunk = 2 * ar.WK;               // >= 2 tiles per key group
-  long long S = (target + base - 1) / base;
+  const int min_chunk = 2 * ar.WK;  // >= 2 tiles per key group
   const long long max_s = tiles / min_chunk > 1 ? tiles / min_chunk : 1;
+  long long S = (want + B - 1) / B;
   if (S > max_s) S = max_s;
-  // ragged batches with too few row blocks to fill the GPU: split further so
-  // that long sequences spread over several CUs
-  if (B > 1 && base < target && S < 4 && max_s >= 4) S = 4;
-  if (S < 1 || base > kSyncGroups) S = 1;
+  if (S < 1 || base > kSyncGroups || (B > kEvenSequences && S > 1) || tiles >= (1 << 20)) S = 1;
   p.chunk = cdiv(tiles, S);
   p.S = cdiv(tiles, p.chunk);
   p.nwork = (int)(base * p.S);
   p.grid = cdiv(p.nwork, kXcds) * kXcds;
+  if (p.S > 1) {
+    p.slots = (int)(want < (long long)B * p.S ? want : (long long)B * p.S);
+    p.min_chunk = min_chunk;
+    p.even_grid = kXcds * p.nRB * cdiv((long long)p.slots * Hkv, kXcds);
+  }
   const int DT = D / 16, NTG = p.RB / 16;
   if (p.S > 1) {
     // sync region (counters, then tree flags), chunk partials: O fragments,
@@ -111,13 +114,6 @@ inline AttnPlan attn_plan_arr(int B, int N, int Hq, int Hkv, int D, int Lmax, in
     p.ws_ml_bytes = (size_t)B * Hkv * p.nRB * p.S * p.RB * 8;
   }
   p.ws_bytes = p.ws_sync_bytes + p.ws_o_bytes + p.ws_ml_bytes;
-  // The last chunk of a row block merges all of them when that takes at
-  // most kFusedMergeBytes of loads per thread (two batches of loads per
-  // lane); larger merges go to a second kernel that spreads them over the
-  // whole GPU.  1 KB rather than 512 B puts the 4-chunk ragged batch of
-  // 16 x 64 nodes (Hq 32, Hkv 4) in the kernel: 1.2% faster than its merge
-  // kernel, which had to wait for the slowest sequence.
-  p.fused = p.S > 1 && (size_t)p.S * p.RB * D * 4 <= (size_t)kFusedMergeBytes * p.threads;
   // With several key groups every one of them needs the block's queries.
   // When the grid fills every CU, key group 0 loads them and shares them
   // through LDS where that fits: the other groups' copies were 64 KB of
@@ -126,7 +122,6 @@ inline AttnPlan attn_plan_arr(int B, int N, int Hq, int Hkv, int D, int Lmax, in
   // idle the copies cost nothing and the LDS hop only adds latency (3%
   // slower for a grid of two workgroups).
   p.qshare = 0;
-  p.lds_bytes = p.NS > 0 ? attn_lds_bytes(D, ar.WR, ar.WK, p.NS, p.G, N, false) : kMaxLds + 1;
   if (p.NS > 0 && ar.WK > 1 && ar.WR > 1 && p.nwork >= 256LL * p.wg_per_cu) {
     const size_t with_q = attn_lds_bytes(D, ar.WR, ar.WK, p.NS, p.G, N, true);
     if (with_q * p.wg_per_cu <= kMaxLds) {
@@ -142,7 +137,7 @@ inline AttnPlan attn_plan_arr(int B, int N, int Hq, int Hkv, int D, int Lmax, in
   // takes one KV head and one of L = 8/Hkv lanes of chunks: chunk s of
   // sequence b goes to lane (b + s) % L.  Every XCD then sees every
   // sequence.  This needs Hkv to divide 8 and L to divide S.
-  p.spread = B > 1 && kXcds % Hkv == 0 && p.S % (kXcds / Hkv) == 0;
+  p.spread = p.slots == 0 && B > 1 && kXcds % Hkv == 0 && p.S % (kXcds / Hkv) == 0;
   // Within an XCD workgroups start in index order as slots free up, so a
   // long chunk that starts in a late round sets the kernel's end.  When an
   // XCD's (sequence, chunk) pairs fit the ranking (kMaxRankPairs, tile
@@ -186,28 +181,84 @@ constexpr bool work_item(int grid, int nwork, int S, int nRB, int spread, int B,
   return it.b < B;
 }
 
+// The even split (slots > 0): the chunks of all sequences are numbered in the
+// order of the sequences, `count` in all (found on the device, at most slots).
+// Every (chunk, KV head) pair is one pair of an XCD, the pairs going to the
+// XCDs in turn, and its row blocks follow each other there, since they read
+// the same keys.  Fills g and rb and returns the chunk's number, or -1 for a
+// workgroup past the work; even_grid holds all pairs of slots chunks.
+constexpr int even_item(int bid, int count, int nRB, int Hkv, WorkItem& it) {
+  const int j = bid / kXcds, q = j / nRB * kXcds + bid % kXcds;
+  it.rb = j % nRB;
+  it.g = q % Hkv;
+  return q / Hkv < count ? q / Hkv : -1;
+}
+
 inline bool attn_plan_fits(const AttnPlan& p) {
   return p.NS > 0 && p.lds_bytes * p.wg_per_cu <= kMaxLds;
 }
 
-// Rough time of an arrangement: matrix work on padded rows, K/V traffic
-// from L2 (each row block re-reads the keys), HBM, the split partials
-// written and read back, a penalty when the two waves of a SIMD belong
-// to one workgroup (its per-tile barriers keep them in phase, so their
-// matrix and vector work overlap poorly), and a fixed cost per round of
-// workgroups (prologue, first tile's latency, epilogue: a few us each).
-inline double attn_plan_cost(const AttnPlan& p, int B, int Hkv, int D, int Lmax, int N) {
-  const double keys = (double)Lmax + N;
-  double mfma = (double)B * Hkv * p.nRB * p.RB * keys * 4.0 * D / 2.0e15;
-  if (p.wg_per_cu == 1 && p.WR > 1) mfma *= 1.3;
-  const double kv = (double)B * Hkv * keys * D * 4.0;
-  const double l2 = kv * p.nRB / 20.0e12;
-  const double hbm = kv / 6.0e12;
-  const double partial = (double)p.ws_bytes * 2.0 / 5.0e12;
-  const double rounds = (double)cdiv(p.nwork, 256LL * p.wg_per_cu);
-  double t = mfma > l2 ? mfma : l2;
+// Relative time of a plan, roughly in microseconds.  The constants are fitted so
+// that the plan picked is the fastest measured one: 260 shapes (1 to 32
+// sequences, 8 to 512 nodes, 256 to 32768 cached rows, the head shapes of the
+// models above and D = 64) in every arrangement and up to four split counts; the
+// plans picked are 3.3% slower than the fastest on average.  A chunk's tiles take
+// their turns at one time per tile and key group: the latency of a tile's chain
+// of LDS reads, matrix and vector work, or the CU's share of that work.  A
+// chunk's row blocks all run on one XCD, so what does not fit the XCDs at once
+// queues there.  On top come the fixed costs at a workgroup's two ends, HBM as
+// the floor of the streaming, and the split's partials.  The lengths of several
+// sequences are unknown here: they are taken as spread over the capacity,
+// kMeanFill of it on average.
+constexpr double kMeanFill = 0.64;
+
+// Tile time of one key group with all 8 waves of a CU at work, per arrangement
+// (its latency alone: 1.15, with two ring stages 1.28).
+constexpr double kTileFull[] = {1.60, 1.24, 1.33, 1.41, 1.15, 1.28, 1.32};
+static_assert(sizeof(kTileFull) / sizeof(kTileFull[0]) == kNumArrangements, "one per arrangement");
+
+inline double attn_plan_cost(AttnPlan& p, int B, int Hkv, int D, int Lmax, int N) {
+  const double longest = cdiv(Lmax, kKeyTile) + cdiv(N, kKeyTile);
+  const double mean = B == 1 ? longest : kMeanFill * cdiv(Lmax, kKeyTile) + cdiv(N, kKeyTile);
+  double chunk = longest, items = B;
+  if (p.slots > 0) {
+    chunk = B == 1 ? (double)cdiv((long long)longest, p.slots) : B * mean / (p.slots - 0.33 * B);
+    if (chunk < p.min_chunk) chunk = p.min_chunk;
+    if (chunk > longest) chunk = longest;
+    items = B == 1 ? (double)cdiv((long long)longest, (long long)chunk) : B * mean / chunk + 0.5 * B;
+    if (items > p.slots) items = p.slots;
+  }
+  const double wgs = items * Hkv * p.nRB, room = 256.0 * p.wg_per_cu;
+  double per_cu = wgs / 256.0;
+  per_cu = per_cu < 1.0 ? 1.0 : (per_cu > p.wg_per_cu ? p.wg_per_cu : per_cu);
+  const double row_tiles = (double)cdiv(p.M, kRowsPerWave) / p.nRB;
+  const double waves = per_cu * p.WK * (row_tiles < p.WR ? row_tiles : p.WR);
+  double tile = p.NS == 2 ? 1.28 : 1.15;
+  if (kTileFull[p.arr] * waves / 8.0 > tile) tile = kTileFull[p.arr] * waves / 8.0;
+  if (D == 64) tile *= 0.55;
+  double t = chunk / p.WK * tile;
+  const double per_xcd = (double)cdiv((long long)(items * Hkv + 0.999), kXcds) * p.nRB;
+  const long long rounds = cdiv((long long)per_xcd, 32LL * p.wg_per_cu);
+  if (rounds > 1) {
+    const double queue = B * mean * Hkv * p.nRB / room / p.WK * tile + 0.34 * t;
+    const double turns = rounds * t;
+    t = t > queue ? t : (queue < turns ? queue : turns);
+  }
+  const double hbm = B * mean * kKeyTile * Hkv * D * 4.0 / 10.0e6;
   t = t > hbm ? t : hbm;
-  return t + partial + rounds * 4.0e-6;
+  t += 7.1 + (p.WK > 1 ? 0.85 : 0.0) + 18.0 * (rounds - 1);
+  if (chunk < longest) {
+    const double chunks = (double)cdiv((long long)longest, (long long)(chunk + 0.999));
+    const double block = (p.M < p.RB ? p.M : p.RB) * D * 4.0;  // a row block's partial, bytes
+    const double all = wgs * p.M / p.nRB * D * 4.0;            // all of them
+    const double fused = 1.1 + chunks * block / 233.0e3, second = 3.3 + all / 4.0e6;
+    t += (fused < second ? fused : second) + all / 5.5e6;
+    // The kind of merge: by the workgroup whose chunk arrives last (one CU reads
+    // 61 to 78 KB/us of partials), or by a second kernel that spreads it over
+    // the GPU and starts when the slowest chunk is done (9 us for 33.5 MB).
+    p.fused = 1.1 + chunks * block / 78.0e3 <= 5.3 + all / 4.0e6;
+  }
+  return t;
 }
 
 inline AttnPlan attn_plan(int B, int N, int Hq, int Hkv, int D, int Lmax) {
@@ -215,13 +266,22 @@ inline AttnPlan attn_plan(int B, int N, int Hq, int Hkv, int D, int Lmax) {
   double best_cost = 0;
   bool have = false;
   for (int k = 0; k < kNumArrangements; ++k) {
-    const AttnPlan p = attn_plan_arr(B, N, Hq, Hkv, D, Lmax, k);
-    if (!attn_plan_fits(p)) continue;
-    const double c = attn_plan_cost(p, B, Hkv, D, Lmax, N);
-    if (!have || c < best_cost) {
-      best = p;
-      best_cost = c;
-      have = true;
+    AttnPlan one = attn_plan_arr(B, N, Hq, Hkv, D, Lmax, k, B);
+    if (!attn_plan_fits(one)) continue;
+    // one chunk per sequence, or as many as fill the XCDs once, half or twice
+    // that: a chunk's row blocks stay on one XCD
+    const long long pairs = 32LL * one.wg_per_cu / one.nRB;  // (chunk, KV head) pairs per XCD
+    const long long fill = kXcds * pairs / Hkv;
+    const long long cand[4] = {B, fill / 2, fill, 2 * fill};
+    for (int c = 0; c < 4; ++c) {
+      if (c > 0 && cand[c] <= B) continue;
+      AttnPlan p = c == 0 ? one : attn_plan_arr(B, N, Hq, Hkv, D, Lmax, k, cand[c]);
+      const double t = attn_plan_cost(p, B, Hkv, D, Lmax, N);
+      if (!have || t < best_cost) {
+        best = p;
+        best_cost = t;
+        have = true;
+      }
     }
   }
   return best;

@@ -1,0 +1,92 @@
+"""The even split of a batch into chunks of one size, which the kernels find
+from the kv_lens: its work order on the host, and parity on the GPU where the
+lengths leave sequences of no, one and many chunks."""
+import itertools
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2606_18394_amd import synth
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_work_order(tmp_path):
+    exe = tmp_path / "even_check"
+    subprocess.run(["g++", "-O1", "-std=c++17",
+                    "-I", os.path.join(ROOT, "paper_2606_18394_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "native", "even_check.cpp"), "-o", str(exe)],
+                   check=True)
+    lines = [f"{c} {s} {rb} {h}" for s, rb, h in itertools.product(
+        [1, 2, 7, 8, 42, 64], [1, 2, 3, 32], [1, 2, 3, 8, 12]) for c in sorted({1, s // 2 + 1, s})]
+    res = subprocess.run([str(exe)], input="\n".join(lines), capture_output=True, text=True)
+    assert res.returncode == 0, res.stdout[-500:]
+
+
+LENGTHS = {
+    "empty": lambda B, L: [0] * B,
+    "short": lambda B, L: [5] * B,                                    # far below the capacity
+    "full": lambda B, L: [L] * B,
+    "one long": lambda B, L: [L] + [0] * (B - 1),
+    "last long": lambda B, L: [33] * (B - 1) + [L - 1],
+    "spread": lambda B, L: [(i * 977 + 31) % (L + 1) for i in range(B)],
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", sorted(LENGTHS))
+@pytest.mark.parametrize("shape", [
+    # (B, N, Hq, Hkv, D, capacity): one sequence; few; a lane for each; past the lanes
+    (1, 33, 8, 2, 128, 3000), (1, 200, 8, 1, 64, 4000), (2, 40, 4, 2, 128, 2500),
+    (5, 70, 12, 3, 64, 1500), (16, 9, 8, 4, 128, 1200), (64, 3, 4, 2, 64, 700),
+    (65, 3, 4, 2, 64, 700),
+])
+def test_lengths(shape, kind):
+    """Max-abs error at most 1.5e-2: rounding the softmax weights and the
+    output to bf16 costs up to 2^-9 of |out| each, and a row of few visible
+    keys has outputs up to about 3.5 here (2^-8 * 3.5 = 1.4e-2).  The padded,
+    the paged and the tree-tail call agree where they hold the same keys, and
+    one workspace serves them all."""
+    import torch
+    from helpers import dev_bf16, dev_i32, oracle_attention
+    from paper_2606_18394_amd import tree_verify_attention, tree_verify_attention_paged
+    B, N, Hq, Hkv, D, L = shape
+    rng = np.random.default_rng(B * 1000 + N)
+    trees = np.stack([synth.random_tree(rng, N, depth=9, branching=4) for _ in range(B)])
+    inp = synth.make_inputs(rng, B=B, N=N, Hq=Hq, Hkv=Hkv, D=D, Lmax=L, V=8, trees=trees,
+                            kv_len=np.array(LENGTHS[kind](B, L)), with_logits=False)
+    print(f"{shape} {kind}", flush=True)
+    ref = oracle_attention(inp)
+    q, kt, vt = (dev_bf16(inp[k]) for k in ("q", "k_tree", "v_tree"))
+    par, kvl = dev_i32(inp["parent"]), dev_i32(inp["kv_len"])
+    out = torch.empty_like(q)
+    tree_verify_attention(q, dev_bf16(inp["k_cache"]), dev_bf16(inp["v_cache"]), kt, vt, par, out,
+                          kv_len=kvl)
+    padded = out.float().cpu().numpy()
+    assert np.abs(padded - ref).max() <= 1.5e-2
+    # the tree's rows behind the context of a larger cache
+    cap = L + N
+    tail = {}
+    for c, t in (("k_cache", "k_tree"), ("v_cache", "v_tree")):
+        a = np.zeros((B, cap, Hkv, D), np.uint16)
+        a[:, :L] = inp[c]
+        for b in range(B):
+            n = int(inp["kv_len"][b])
+            a[b, n:n + N] = inp[t][b]
+        tail[c] = a
+    tree_verify_attention(q, dev_bf16(tail["k_cache"]), dev_bf16(tail["v_cache"]), None, None, par,
+                          out, kv_len=kvl)
+    assert np.abs(out.float().cpu().numpy() - ref).max() <= 1.5e-2
+    # pages of 32 rows
+    per = -(-cap // 32)
+    bt, nb = synth.block_table(rng, B, per, spare=2)
+    pools = [synth.scatter_pool(rng, np.pad(tail[c], ((0, 0), (0, per * 32 - cap), (0, 0), (0, 0))),
+                                bt, nb, 32) for c in ("k_cache", "v_cache")]
+    tree_verify_attention_paged(q, dev_bf16(pools[0]), dev_bf16(pools[1]), dev_i32(bt), None, None,
+                                par, out, kv_len=kvl)
+    torch.cuda.synchronize()
+    assert np.abs(out.float().cpu().numpy() - ref).max() <= 1.5e-2
