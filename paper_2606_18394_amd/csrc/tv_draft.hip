@@ -225,10 +225,10 @@ __device__ __forceinline__ int best_head_lane(float v, int i) {
 // fall back to the per-thread lists and W rounds of workgroup argmax.
 constexpr int kTopwCand = kScanThreads;
 
-template <bool F32, int K, bool ONE>
+// L: 16-byte loads per thread and round
+template <bool F32, int K, bool ONE, int L>
 __global__ __launch_bounds__(kScanThreads) void topw_scan(TopwArgs a) {
   constexpr int E = F32 ? 4 : 8;  // elements per chunk
-  constexpr int L = kScanLoadsPerThread;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   __shared__ int s_ncand;
   __shared__ float s_cv[kTopwCand];
@@ -239,8 +239,13 @@ __global__ __launch_bounds__(kScanThreads) void topw_scan(TopwArgs a) {
   const int split = blockIdx.x % a.nsplit;
   const char* rowp = (const char*)a.logits + (size_t)row * a.V * (F32 ? 4 : 2);
   const RowSpan<F32> rs(rowp, a.V);
-  const long long c0 = min((long long)split * a.cps, (long long)rs.chunks);
-  const long long c1 = min(c0 + a.cps, (long long)rs.chunks);
+  // the slice: n chunks from `slice` on, whose first element is row element i0;
+  // offsets inside it fit 32 bits (at least 16 splits of such a row)
+  const int c0 = (int)min((long long)split * a.cps, (long long)rs.chunks);
+  const int n = (int)min(a.cps, (long long)(rs.chunks - c0));
+  // (without chunks the loads go to the workspace and count for nothing)
+  const char* slice = n > 0 ? rs.first + (size_t)c0 * 16 : (const char*)a.part;
+  const int i0 = rs.index(c0);
   const int W = a.W;
 
   TopList<K> top;
@@ -257,9 +262,9 @@ __global__ __launch_bounds__(kScanThreads) void topw_scan(TopwArgs a) {
   const float xt = spare ? load_logit_stream<F32>(rowp, xi) : -INFINITY;
   // rounds are uniform across the workgroup (the first ends at a barrier and
   // always runs, also for a slice without whole chunks)
-  long long cb = c0;
+  int cb = 0;
   do {
-    const long long c = cb + tid;
+    const int c = cb + tid;
     // all L loads are issued first (past the end: the last chunk again),
     // then decoded with the padding replaced by -inf bit patterns, so the
     // loads are in flight together
@@ -267,14 +272,13 @@ __global__ __launch_bounds__(kScanThreads) void topw_scan(TopwArgs a) {
     uint4 raw[L];
 #pragma unroll
     for (int u = 0; u < L; ++u) {
-      const long long cu = c + (long long)u * kScanThreads;
-      const long long cl = cu < c1 ? cu : c1 - 1;
-      if (rs.chunks > 0) raw[u] = rs.load(cl);
+      const int cu = c + u * kScanThreads;
+      raw[u] = load_stream16(slice + (unsigned)max(min(cu, n - 1), 0) * 16u);
     }
     float x[L][E];
 #pragma unroll
     for (int u = 0; u < L; ++u) {
-      const bool in = c + (long long)u * kScanThreads < c1;
+      const bool in = c + u * kScanThreads < n;
       const unsigned int ws[4] = {in ? raw[u].x : kNegInf, in ? raw[u].y : kNegInf,
                                   in ? raw[u].z : kNegInf, in ? raw[u].w : kNegInf};
 #pragma unroll
@@ -287,7 +291,7 @@ __global__ __launch_bounds__(kScanThreads) void topw_scan(TopwArgs a) {
         }
       }
     }
-    const bool extra = spare && (tid < rs.head ? cb == c0 : cb + (long long)L * kScanThreads >= c1);
+    const bool extra = spare && (tid < rs.head ? cb == 0 : cb + L * kScanThreads >= n);
     const float xe = extra ? xt : -INFINITY;
     float bmu[L];  // maximum of each load
     float bm = xe;
@@ -308,7 +312,7 @@ __global__ __launch_bounds__(kScanThreads) void topw_scan(TopwArgs a) {
       s = (m == -INFINITY ? 0.f : s * __expf(m - mn)) + bs;
       m = mn;
     }
-    if (cb == c0) {
+    if (cb == 0) {
       // Each wave's q-th largest thread maximum, q = ceil(W / waves): every
       // wave holds q elements at least that large, so at least W elements
       // of the slice are >= the smallest of these.
@@ -334,15 +338,15 @@ __global__ __launch_bounds__(kScanThreads) void topw_scan(TopwArgs a) {
       if (bm >= tau) {
 #pragma unroll
         for (int u = 0; u < L; ++u) {
-          const long long cu = c + (long long)u * kScanThreads;
-          if (cu < c1 && bmu[u] >= tau) {
+          const int cu = c + u * kScanThreads;
+          if (cu < n && bmu[u] >= tau) {
 #pragma unroll
             for (int e = 0; e < E; ++e)
               if (x[u][e] >= tau) {
                 const int slot = atomicAdd(&s_ncand, 1);
                 if (slot < kTopwCand) {
                   s_cv[slot] = x[u][e];
-                  s_ci[slot] = rs.index(cu) + e;
+                  s_ci[slot] = i0 + cu * E + e;
                 }
               }
           }
@@ -364,15 +368,15 @@ __global__ __launch_bounds__(kScanThreads) void topw_scan(TopwArgs a) {
       if (extra && before && xe >= tau && xe > top.thr()) top.insert(xe, xi);
 #pragma unroll
       for (int u = 0; u < L; ++u) {
-        const long long cu = c + (long long)u * kScanThreads;
+        const int cu = c + u * kScanThreads;
 #pragma unroll
         for (int e = 0; e < E; ++e)
-          if (x[u][e] >= tau && x[u][e] > top.thr()) top.insert(x[u][e], rs.index(cu) + e);
+          if (x[u][e] >= tau && x[u][e] > top.thr()) top.insert(x[u][e], i0 + cu * E + e);
       }
       if (extra && !before && xe >= tau && xe > top.thr()) top.insert(xe, xi);
     }
-    cb += (long long)L * kScanThreads;
-  } while (cb < c1);
+    cb += L * kScanThreads;
+  } while (cb < n);
 
   // workgroup: (m, s) by shuffles and LDS, the top-W by W rounds of argmax
   __shared__ float red_m[kScanThreads / 64], red_s[kScanThreads / 64];
@@ -470,17 +474,24 @@ __global__ __launch_bounds__(64) void topw_finish(TopwArgs a) {
   }
 }
 
-template <bool ONE>
-static void launch_topw_scan(bool f32, int K, dim3 g, dim3 t, hipStream_t st, const TopwArgs& a) {
-  if (f32) {
-    if (K == 4) hipLaunchKernelGGL((topw_scan<true, 4, ONE>), g, t, 0, st, a);
-    else if (K == 8) hipLaunchKernelGGL((topw_scan<true, 8, ONE>), g, t, 0, st, a);
-    else hipLaunchKernelGGL((topw_scan<true, kTopwMax, ONE>), g, t, 0, st, a);
-  } else {
-    if (K == 4) hipLaunchKernelGGL((topw_scan<false, 4, ONE>), g, t, 0, st, a);
-    else if (K == 8) hipLaunchKernelGGL((topw_scan<false, 8, ONE>), g, t, 0, st, a);
-    else hipLaunchKernelGGL((topw_scan<false, kTopwMax, ONE>), g, t, 0, st, a);
-  }
+template <bool F32, bool ONE, int L>
+static void launch_topw_scan_k(int K, dim3 g, hipStream_t st, const TopwArgs& a) {
+  const dim3 t(kScanThreads);
+  if (K == 4) hipLaunchKernelGGL((topw_scan<F32, 4, ONE, L>), g, t, 0, st, a);
+  else if (K == 8) hipLaunchKernelGGL((topw_scan<F32, 8, ONE, L>), g, t, 0, st, a);
+  else hipLaunchKernelGGL((topw_scan<F32, kTopwMax, ONE, L>), g, t, 0, st, a);
+}
+
+// The fewest loads per thread that take a slice in one round (a load past the
+// slice costs what one inside it does), else several rounds of the most.
+template <bool F32>
+static void launch_topw_scan(int K, dim3 g, hipStream_t st, const TopwArgs& a) {
+  constexpr int E = F32 ? 4 : 8, kFull = kTopwRound / E;
+  const long long loads = (a.cps + kScanThreads - 1) / kScanThreads;
+  if (loads <= 24 / E) launch_topw_scan_k<F32, true, 24 / E>(K, g, st, a);
+  else if (loads <= 40 / E) launch_topw_scan_k<F32, true, 40 / E>(K, g, st, a);
+  else if (loads <= kFull) launch_topw_scan_k<F32, true, kFull>(K, g, st, a);
+  else launch_topw_scan_k<F32, false, kFull>(K, g, st, a);
 }
 
 hipError_t launch_topw(const void* logits, int f32, int B, int Nd, int V, int W, int32_t* tok,
@@ -497,12 +508,10 @@ hipError_t launch_topw(const void* logits, int f32, int B, int Nd, int V, int W,
   a.W = W;
   a.nsplit = p.nsplit;
   a.cps = p.chunks_per_split;
-  const dim3 g(p.grid), t(kScanThreads);
+  const dim3 g(p.grid);
   const int K = W <= 4 ? 4 : (W <= 8 ? 8 : 16);
-  // one load round per workgroup: every split's slice fits in one
-  const bool one = p.chunks_per_split <= (long long)kScanThreads * kScanLoadsPerThread;
-  if (one) launch_topw_scan<true>(f32 != 0, K, g, t, st, a);
-  else launch_topw_scan<false>(f32 != 0, K, g, t, st, a);
+  if (f32) launch_topw_scan<true>(K, g, st, a);
+  else launch_topw_scan<false>(K, g, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (K == 4) hipLaunchKernelGGL(topw_finish<4>, dim3(a.rows), dim3(64), 0, st, a);

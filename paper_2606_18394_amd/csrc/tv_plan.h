@@ -376,10 +376,14 @@ inline size_t accept_ws_bytes(int B, int N) {
 // Draft top-W (tree drafting's candidates): one workgroup per (draft-depth
 // row, vocabulary split) reduces its slice to a running log-sum-exp state
 // and its W best (value, token) pairs; a second kernel merges the splits of
-// each row.  Splits as in the acceptance scan.
+// each row.  A slice is one round of loads wherever 16 splits allow it (the
+// scan of more rounds keeps lists and runs several times longer), and where
+// that leaves the GPU short of workgroups, up to 16 splits of fewer loads per
+// thread.
 constexpr int kTopwMax = 16;             // largest branching width W
 constexpr int kMaxDraftDepth = 64;       // == TV_MAX_DRAFT_DEPTH
 constexpr size_t kTopwPartBytes = 8 + 8 * kTopwMax;
+constexpr int kTopwRound = 64;           // logits a thread reads in one round, at most
 
 struct TopwPlan {
   int nsplit;
@@ -392,10 +396,11 @@ inline TopwPlan topw_plan(int B, int Nd, int V, int vec_elems) {
   TopwPlan p{};
   const long long rows = (long long)B * Nd;
   const long long chunks = (V + vec_elems - 1) / vec_elems;
-  long long ns = accept_split_cap(rows);
-  const long long per_round = (long long)kScanThreads * kScanLoadsPerThread;
-  const long long by_size = (chunks + per_round - 1) / per_round;
-  if (ns > by_size) ns = by_size;
+  const long long per_round = (long long)kScanThreads * kTopwRound / vec_elems;
+  long long ns = (chunks + per_round - 1) / per_round;
+  const long long fill = (512 + rows - 1) / rows, whole = chunks / kScanThreads;  // >= 1 load each
+  if (ns < fill) ns = fill < whole ? fill : whole;
+  if (ns > kAcceptMaxSplit) ns = kAcceptMaxSplit;
   if (ns < 1) ns = 1;
   p.chunks_per_split = (chunks + ns - 1) / ns;
   p.nsplit = (int)((chunks + p.chunks_per_split - 1) / p.chunks_per_split);
@@ -405,8 +410,7 @@ inline TopwPlan topw_plan(int B, int Nd, int V, int vec_elems) {
 }
 
 inline size_t topw_ws_bytes(int B, int Nd) {
-  const long long rows = (long long)B * Nd;
-  return (size_t)(rows * accept_split_cap(rows)) * kTopwPartBytes;
+  return (size_t)B * Nd * kAcceptMaxSplit * kTopwPartBytes;
 }
 
 // Non-greedy acceptance: an lse scan over the B*N target rows (splits as

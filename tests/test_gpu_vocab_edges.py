@@ -72,3 +72,21 @@ def test_rows_from_any_element(dtype, offset):
         for b in range(B):
             if res[3]["gap"][b] >= 1e-3:
                 assert corr[b] == res[2][b], (V, b)
+
+
+@pytest.mark.parametrize("shape", [
+    # (B, Nd, V, dtype): 3, 5 and 8 (6, 10 and 16) loads per thread in one
+    # round, then several rounds
+    (1, 3, 90000, "bf16"), (2, 4, 151937, "bf16"), (1, 2, 262140, "bf16"), (1, 2, 262200, "bf16"),
+    (1, 3, 90001, "f32"), (2, 4, 151937, "f32"), (1, 2, 262143, "f32"), (1, 2, 300003, "f32"),
+    (40, 16, 16391, "bf16"), (40, 16, 32800, "f32"),
+])
+def test_topw_rounds(shape):
+    from paper_2606_18394_amd import draft_topw
+    B, Nd, V, dtype = shape
+    print(shape, flush=True)
+    lg, ref = _rows(np.random.default_rng(V), B, Nd, V, dtype, 0)
+    t, lp = (y.cpu().numpy() for y in draft_topw(lg, 8))
+    rt, rlp = oracle.draft_topw(ref, 8)
+    np.testing.assert_array_equal(t, rt)
+    assert np.abs(lp - rlp).max() <= 1e-5
