@@ -8,6 +8,7 @@ or the tensors are not on a GPU, the calls raise.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 import threading
 
@@ -94,10 +95,16 @@ def _check(rc: int) -> None:
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _need(t, name, dtype, shape=None, device=None):
+    # the checks that pass come first and are cheap ones: a call makes up to
+    # nine of these, and at the small sizes the host's time per call counts
+    if (isinstance(t, torch.Tensor) and t.dtype is dtype and t.is_cuda and t.is_contiguous()
+            and (shape is None or t.shape == shape)
+            and (device is None or t.get_device() == device.index)):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.dtype != dtype:
@@ -112,6 +119,35 @@ def _need(t, name, dtype, shape=None, device=None):
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
 
 
+def _output(t, name, dtype, shape, device):
+    """The caller's output tensor, checked, or a new one."""
+    if t is None:
+        return torch.empty(shape, dtype=dtype, device=device)
+    _need(t, name, dtype, shape, device)
+    return t
+
+
+def _stream(device) -> int:
+    """The current stream of a GPU tensor's device, as an address."""
+    return _raw_stream(device.index)
+
+
+try:
+    _raw_stream = torch._C._cuda_getCurrentRawStream
+except AttributeError:  # a torch without GPU support: the calls refuse its tensors
+    def _raw_stream(index):
+        return torch.cuda.current_stream(index).cuda_stream
+
+
+@functools.lru_cache(maxsize=1024)
+def _bytes(query: str, *sizes) -> int:
+    """A workspace query's answer, which depends on its sizes alone."""
+    need = getattr(load_library(), query)(*sizes)
+    if need == 0:
+        _check(-2)
+    return need
+
+
 def _need_tree(k_tree, v_tree, shape, device):
     """Tree K/V tensors, or both None (tree-tail layout)."""
     if (k_tree is None) != (v_tree is None):
@@ -122,6 +158,9 @@ def _need_tree(k_tree, v_tree, shape, device):
 
 
 _retired = []
+
+
+_device_name = functools.lru_cache(maxsize=64)(str)
 
 
 def workspace(kind: str, nbytes: int, device, stream_ptr: int) -> torch.Tensor:
@@ -135,7 +174,7 @@ def workspace(kind: str, nbytes: int, device, stream_ptr: int) -> torch.Tensor:
     enough (make one eager call of the same or a larger size on the capturing
     stream first), or the caller passes ``workspace_tensor``.
     """
-    key = (kind, str(device), stream_ptr)
+    key = (kind, _device_name(device), stream_ptr)
     ws = _workspaces.get(key)
     if ws is None or ws.numel() < nbytes:
         if torch.device(device).type == "cuda" and torch.cuda.is_current_stream_capturing():
@@ -172,15 +211,13 @@ def tree_verify_attention(q, k_cache, v_cache, k_tree, v_tree, parent, out,
     _need(out, "out", torch.bfloat16, (B, N, Hq, D), dev)
     if kv_len is not None:
         _need(kv_len, "kv_len", torch.int32, (B,), dev)
-    stream = torch.cuda.current_stream(dev).cuda_stream
-    need = lib.tv_tree_verify_attention_workspace(B, N, Hq, Hkv, D, Lmax)
-    if need == 0:
-        _check(-2)
+    stream = _stream(dev)
+    need = _bytes("tv_tree_verify_attention_workspace", B, N, Hq, Hkv, D, Lmax)
     ws = workspace_tensor if workspace_tensor is not None else workspace("attn", need, dev, stream)
     _check(lib.tv_tree_verify_attention(
         _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(k_tree), _ptr(v_tree), _ptr(parent),
         _ptr(kv_len), _ptr(out), B, N, Hq, Hkv, D, Lmax,
-        0.0 if scale is None else float(scale), _ptr(ws), ws.numel(), ctypes.c_void_p(stream)))
+        0.0 if scale is None else float(scale), _ptr(ws), ws.numel(), stream))
     return out
 
 
@@ -206,15 +243,13 @@ def tree_verify_attention_paged(q, k_pool, v_pool, block_table, k_tree, v_tree, 
     _need(out, "out", torch.bfloat16, (B, N, Hq, D), dev)
     if kv_len is not None:
         _need(kv_len, "kv_len", torch.int32, (B,), dev)
-    stream = torch.cuda.current_stream(dev).cuda_stream
-    need = lib.tv_tree_verify_attention_workspace(B, N, Hq, Hkv, D, max_blocks * bs)
-    if need == 0:
-        _check(-2)
+    stream = _stream(dev)
+    need = _bytes("tv_tree_verify_attention_workspace", B, N, Hq, Hkv, D, max_blocks * bs)
     ws = workspace_tensor if workspace_tensor is not None else workspace("attn", need, dev, stream)
     _check(lib.tv_tree_verify_attention_paged(
         _ptr(q), _ptr(k_pool), _ptr(v_pool), _ptr(block_table), bs, max_blocks, num_blocks,
         _ptr(k_tree), _ptr(v_tree), _ptr(parent), _ptr(kv_len), _ptr(out), B, N, Hq, Hkv, D,
-        0.0 if scale is None else float(scale), _ptr(ws), ws.numel(), ctypes.c_void_p(stream)))
+        0.0 if scale is None else float(scale), _ptr(ws), ws.numel(), stream))
     return out
 
 
@@ -236,15 +271,13 @@ def block_causal_attention(q, k_ctx, v_ctx, k_blk, v_blk, anchors, out, scale=No
     _need(v_blk, "v_blk", torch.bfloat16, (B, A, S, Hkv, D), dev)
     _need(anchors, "anchors", torch.int32, (B, A), dev)
     _need(out, "out", torch.bfloat16, (B, A, S, Hq, D), dev)
-    stream = torch.cuda.current_stream(dev).cuda_stream
-    need = lib.tv_block_causal_attention_workspace(B, A, S, Hq, Hkv, D, L)
-    if need == 0:
-        _check(-2)
+    stream = _stream(dev)
+    need = _bytes("tv_block_causal_attention_workspace", B, A, S, Hq, Hkv, D, L)
     ws = workspace_tensor if workspace_tensor is not None else workspace("attn", need, dev, stream)
     _check(lib.tv_block_causal_attention(
         _ptr(q), _ptr(k_ctx), _ptr(v_ctx), _ptr(k_blk), _ptr(v_blk), _ptr(anchors), _ptr(out),
         B, A, S, Hq, Hkv, D, L, 0.0 if scale is None else float(scale), _ptr(ws), ws.numel(),
-        ctypes.c_void_p(stream)))
+        stream))
     return out
 
 
@@ -270,26 +303,18 @@ def tree_accept_sampled(logits, draft_tok, parent, u_accept, seed, temperature, 
     _need(draft_tok, "draft_tok", torch.int32, (B, N), dev)
     _need(parent, "parent", torch.int32, (B, N), dev)
     _need(u_accept, "u_accept", torch.float32, (B, N), dev)
-    if accept_len is None:
-        accept_len = torch.empty(B, dtype=torch.int32, device=dev)
-    if path is None:
-        path = torch.empty(B, Dmax, dtype=torch.int32, device=dev)
-    if correction is None:
-        correction = torch.empty(B, dtype=torch.int32, device=dev)
-    _need(accept_len, "accept_len", torch.int32, (B,), dev)
-    _need(path, "path", torch.int32, (B, Dmax), dev)
-    _need(correction, "correction", torch.int32, (B,), dev)
-    stream = torch.cuda.current_stream(dev).cuda_stream
-    need = lib.tv_tree_accept_sampled_workspace(B, N, V)
-    if need == 0:
-        _check(-2)
+    accept_len = _output(accept_len, "accept_len", torch.int32, (B,), dev)
+    path = _output(path, "path", torch.int32, (B, Dmax), dev)
+    correction = _output(correction, "correction", torch.int32, (B,), dev)
+    stream = _stream(dev)
+    need = _bytes("tv_tree_accept_sampled_workspace", B, N, V)
     ws = workspace_tensor if workspace_tensor is not None else workspace("sample", need, dev,
                                                                          stream)
     _check(lib.tv_tree_accept_sampled(
         _ptr(logits), dt, _ptr(draft_tok), _ptr(parent), _ptr(u_accept),
         ctypes.c_ulonglong(int(seed) & 0xFFFFFFFFFFFFFFFF), ctypes.c_float(temperature), B, N, V,
         Dmax, _ptr(accept_len), _ptr(path), _ptr(correction), _ptr(ws), ws.numel(),
-        ctypes.c_void_p(stream)))
+        stream))
     return accept_len, path, correction
 
 
@@ -317,10 +342,10 @@ def commit_path(k_tree, v_tree, path, accept_len, k_cache, v_cache, kv_len, n_no
     _need(k_cache, "k_cache", torch.bfloat16, (B, Lmax, Hkv, D), dev)
     _need(v_cache, "v_cache", torch.bfloat16, (B, Lmax, Hkv, D), dev)
     _need(kv_len, "kv_len", torch.int32, (B,), dev)
-    stream = torch.cuda.current_stream(dev).cuda_stream
+    stream = _stream(dev)
     _check(lib.tv_commit_path(
         _ptr(k_tree), _ptr(v_tree), _ptr(path), _ptr(accept_len), _ptr(k_cache), _ptr(v_cache),
-        _ptr(kv_len), B, N, Hkv, D, Lmax, Dmax, ctypes.c_void_p(stream)))
+        _ptr(kv_len), B, N, Hkv, D, Lmax, Dmax, stream))
 
 
 def commit_path_paged(k_tree, v_tree, path, accept_len, k_pool, v_pool, block_table, kv_len,
@@ -340,11 +365,11 @@ def commit_path_paged(k_tree, v_tree, path, accept_len, k_pool, v_pool, block_ta
     _need(v_pool, "v_pool", torch.bfloat16, (num_blocks, bs, Hkv, D), dev)
     _need(block_table, "block_table", torch.int32, (B, max_blocks), dev)
     _need(kv_len, "kv_len", torch.int32, (B,), dev)
-    stream = torch.cuda.current_stream(dev).cuda_stream
+    stream = _stream(dev)
     _check(lib.tv_commit_path_paged(
         _ptr(k_tree), _ptr(v_tree), _ptr(path), _ptr(accept_len), _ptr(k_pool), _ptr(v_pool),
         _ptr(block_table), bs, max_blocks, num_blocks, _ptr(kv_len), B, N, Hkv, D, Dmax,
-        ctypes.c_void_p(stream)))
+        stream))
 
 
 def tree_accept(logits, draft_tok, parent, Dmax, accept_len=None, path=None,
@@ -363,25 +388,17 @@ def tree_accept(logits, draft_tok, parent, Dmax, accept_len=None, path=None,
     _need(logits, "logits", logits.dtype, device=dev)
     _need(draft_tok, "draft_tok", torch.int32, (B, N), dev)
     _need(parent, "parent", torch.int32, (B, N), dev)
-    if accept_len is None:
-        accept_len = torch.empty(B, dtype=torch.int32, device=dev)
-    if path is None:
-        path = torch.empty(B, Dmax, dtype=torch.int32, device=dev)
-    if tgt_argmax is None and with_argmax:
-        tgt_argmax = torch.empty(B, N, dtype=torch.int32, device=dev)
-    _need(accept_len, "accept_len", torch.int32, (B,), dev)
-    _need(path, "path", torch.int32, (B, Dmax), dev)
-    if tgt_argmax is not None:
-        _need(tgt_argmax, "tgt_argmax", torch.int32, (B, N), dev)
-    stream = torch.cuda.current_stream(dev).cuda_stream
-    need = lib.tv_tree_accept_workspace(B, N, V)
-    if need == 0:
-        _check(-2)
+    accept_len = _output(accept_len, "accept_len", torch.int32, (B,), dev)
+    path = _output(path, "path", torch.int32, (B, Dmax), dev)
+    if tgt_argmax is not None or with_argmax:
+        tgt_argmax = _output(tgt_argmax, "tgt_argmax", torch.int32, (B, N), dev)
+    stream = _stream(dev)
+    need = _bytes("tv_tree_accept_workspace", B, N, V)
     ws = workspace_tensor if workspace_tensor is not None else workspace("accept", need, dev, stream)
     _check(lib.tv_tree_accept(
         _ptr(logits), dt, _ptr(draft_tok), _ptr(parent), B, N, V, int(Dmax),
         _ptr(accept_len), _ptr(path), _ptr(tgt_argmax), _ptr(ws), ws.numel(),
-        ctypes.c_void_p(stream)))
+        stream))
     return accept_len, path, tgt_argmax
 
 
@@ -405,10 +422,10 @@ def tree_accept_noalloc(logits, draft_tok, parent, Dmax, accept_len, path, tgt_a
     _need(path, "path", torch.int32, (B, Dmax), dev)
     if tgt_argmax is not None:
         _need(tgt_argmax, "tgt_argmax", torch.int32, (B, N), dev)
-    stream = torch.cuda.current_stream(dev).cuda_stream
+    stream = _stream(dev)
     _check(lib.tv_tree_accept_noalloc(
         _ptr(logits), dt, _ptr(draft_tok), _ptr(parent), B, N, V, int(Dmax),
-        _ptr(accept_len), _ptr(path), _ptr(tgt_argmax), ctypes.c_void_p(stream)))
+        _ptr(accept_len), _ptr(path), _ptr(tgt_argmax), stream))
     return accept_len, path, tgt_argmax
 
 
@@ -426,19 +443,13 @@ def draft_topw(logits, W, tok=None, logp=None, workspace_tensor=None):
     else:
         raise TypeError("logits must be bfloat16 or float32")
     _need(logits, "logits", logits.dtype, device=dev)
-    if tok is None:
-        tok = torch.empty(B, Nd, W, dtype=torch.int32, device=dev)
-    if logp is None:
-        logp = torch.empty(B, Nd, W, dtype=torch.float32, device=dev)
-    _need(tok, "tok", torch.int32, (B, Nd, W), dev)
-    _need(logp, "logp", torch.float32, (B, Nd, W), dev)
-    stream = torch.cuda.current_stream(dev).cuda_stream
-    need = lib.tv_draft_topw_workspace(B, Nd, V)
-    if need == 0:
-        _check(-2)
+    tok = _output(tok, "tok", torch.int32, (B, Nd, W), dev)
+    logp = _output(logp, "logp", torch.float32, (B, Nd, W), dev)
+    stream = _stream(dev)
+    need = _bytes("tv_draft_topw_workspace", B, Nd, V)
     ws = workspace_tensor if workspace_tensor is not None else workspace("topw", need, dev, stream)
     _check(lib.tv_draft_topw(_ptr(logits), dt, B, Nd, V, int(W), _ptr(tok), _ptr(logp),
-                             _ptr(ws), ws.numel(), ctypes.c_void_p(stream)))
+                             _ptr(ws), ws.numel(), stream))
     return tok, logp
 
 
@@ -458,8 +469,8 @@ def build_tree(tok, logp, budget, root_tok=None, with_score=True):
     depth = torch.empty(B, budget, dtype=torch.int32, device=dev)
     score = torch.empty(B, budget, dtype=torch.float32, device=dev) if with_score else None
     n_nodes = torch.empty(B, dtype=torch.int32, device=dev)
-    stream = torch.cuda.current_stream(dev).cuda_stream
+    stream = _stream(dev)
     _check(lib.tv_build_tree(_ptr(tok), _ptr(logp), _ptr(root_tok), B, Nd, W, int(budget),
                              _ptr(parent), _ptr(token), _ptr(depth), _ptr(score), _ptr(n_nodes),
-                             ctypes.c_void_p(stream)))
+                             stream))
     return parent, token, depth, score, n_nodes
