@@ -21,6 +21,9 @@ hipError_t launch_attention(const void* q, const void* kc, const void* vc, const
                             float scale, void* ws, const AttnPlan& p, hipStream_t st,
                             const int32_t* block_table, int block_shift, int max_blocks,
                             int num_blocks, int cgroup);
+hipError_t launch_packed(const void* q, const void* kc, const void* vc, const void* kt, const void* vt,
+                         const int32_t* anchors, void* out, int B, int A, int S, int Hq, int Hkv, int D,
+                         int L, float scale, void* ws, const PackPlan& p, hipStream_t st);
 hipError_t launch_commit(const void* kt, const void* vt, const int32_t* path,
                          const int32_t* accept_len, void* kc, void* vc, int32_t* kv_len,
                          const int32_t* block_table, int shift, int max_blocks, int num_blocks,
@@ -163,6 +166,8 @@ int tv_tree_verify_attention(const void* q, const void* k_cache, const void* v_c
 size_t tv_block_causal_attention_workspace(int B, int A, int S, int Hq, int Hkv, int D,
                                           int L) {
   if (check_block_causal(B, A, S, Hq, Hkv, D, L) != TV_OK) return 0;
+  const tv::PackPlan pk = tv::pack_plan(B, A, S, Hq, Hkv);
+  if (pk.nb > 0) return pk.ws_bytes;
   const tv::AttnPlan& p = attn_plan_of(B * A, S, Hq, Hkv, D, L);
   return p.ws_bytes > 0 ? p.ws_bytes : 256;
 }
@@ -179,10 +184,18 @@ int tv_block_causal_attention(const void* q, const void* k_ctx, const void* v_ct
   if (misaligned(q) || misaligned(k_blk) || misaligned(v_blk) || misaligned(out) ||
       (L > 0 && (misaligned(k_ctx) || misaligned(v_ctx))))
     return TV_ERR_ALIGN;
+  if (!(scale > 0.f)) scale = 1.0f / sqrtf((float)D);
+  const tv::PackPlan pk = tv::pack_plan(B, A, S, Hq, Hkv);
+  if (pk.nb > 0) {
+    if (!workspace || workspace_bytes < pk.ws_bytes) return TV_ERR_WORKSPACE;
+    if (misaligned(workspace)) return TV_ERR_ALIGN;
+    const hipError_t e = tv::launch_packed(q, k_ctx, v_ctx, k_blk, v_blk, anchors, out, B, A, S, Hq,
+                                           Hkv, D, L, scale, workspace, pk, stream);
+    return e == hipSuccess ? TV_OK : TV_ERR_LAUNCH;
+  }
   const tv::AttnPlan& p = attn_plan_of(B * A, S, Hq, Hkv, D, L);
   if (p.ws_bytes > 0 && (!workspace || workspace_bytes < p.ws_bytes)) return TV_ERR_WORKSPACE;
   if (misaligned(workspace)) return TV_ERR_ALIGN;
-  if (!(scale > 0.f)) scale = 1.0f / sqrtf((float)D);
   hipError_t e = tv::launch_attention(q, k_ctx, v_ctx, k_blk, v_blk, nullptr, anchors, out,
                                       B * A, S, Hq, Hkv, D, L, scale, workspace, p, stream,
                                       nullptr, 0, 0, 0, A);

@@ -448,7 +448,7 @@ __device__ __forceinline__ void issue_tile(const TreeSrc& src, const uint32_t (&
 
 // Where a tile's scores need masking: the cache tail and the tree tiles.
 struct MaskInfo {
-  int t, nct, kvl, ntt, g4, tail;
+  int t, nct, kvl, ntt, tail;
   const uint32_t* anc;
 };
 
@@ -500,11 +500,18 @@ __device__ __forceinline__ void tile_scores(const bf16x8 (&kf)[2][D / 32], const
   }
 }
 
-// mask: -inf for cache keys at or past kv_len and for tree keys outside
-// the row's ancestor-or-self set (one 32-bit word of its bitmask per tile).
+// The first n keys of a tile (n < 0: none, n > 32: all) as a visibility word.
+__device__ __forceinline__ uint32_t first_keys(int n) {
+  n = n < 0 ? 0 : (n > kKeyTile ? kKeyTile : n);
+  return (uint32_t)((1ull << n) - 1ull);
+}
+
+// The visible keys of tile mk.t for this lane's row of every 16-row tile, one
+// bit per key: cache keys below kv_len, and tree keys of the row's
+// ancestor-or-self set (one 32-bit word of its bitmask per tile).
 template <int NT>
-__device__ __forceinline__ void tile_mask(f32x4 (&sc)[2][NT], const MaskInfo& mk,
-                                          const int (&node_rel)[NT]) {
+__device__ __forceinline__ void tile_bits(const MaskInfo& mk, const int (&node_rel)[NT],
+                                          uint32_t (&bits)[NT]) {
   if (mk.tail) {
     // Tree-tail layout: key k of the tile is node s + k (s < 0: a context
     // row).  Its visibility bits are a 32-bit window of the row's ancestor
@@ -517,35 +524,27 @@ __device__ __forceinline__ void tile_mask(f32x4 (&sc)[2][NT], const MaskInfo& mk
       const uint32_t* wp = mk.anc + node_rel[nt] * mk.ntt;
       const uint32_t lo = w0 < 0 ? 0xFFFFFFFFu : wp[w0];
       const uint32_t hi = w0 + 1 < mk.ntt ? wp[w0 + 1] : 0u;
-      const uint32_t bits = (uint32_t)((((uint64_t)hi << 32) | lo) >> sh);
-#pragma unroll
-      for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (!((bits >> (16 * tt + 4 * mk.g4 + j)) & 1u)) sc[tt][nt][j] = -INFINITY;
+      bits[nt] = (uint32_t)((((uint64_t)hi << 32) | lo) >> sh);
     }
   } else if (mk.t < mk.nct) {
 #pragma unroll
+    for (int nt = 0; nt < NT; ++nt) bits[nt] = first_keys(mk.kvl - mk.t * kKeyTile);
+  } else {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) bits[nt] = mk.anc[node_rel[nt] * mk.ntt + mk.t - mk.nct];
+  }
+}
+
+// mask: -inf for the keys a row does not see.
+template <int NT>
+__device__ __forceinline__ void tile_mask(f32x4 (&sc)[2][NT], const uint32_t (&bits)[NT], int g4) {
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
     for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const bool vis = mk.t * kKeyTile + 16 * tt + 4 * mk.g4 + j < mk.kvl;
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-          if (!vis) sc[tt][nt][j] = -INFINITY;
-      }
-  } else {
-    const int word = mk.t - mk.nct;
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      const uint32_t bits = mk.anc[node_rel[nt] * mk.ntt + word];
-#pragma unroll
-      for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (!((bits >> (16 * tt + 4 * mk.g4 + j)) & 1u)) sc[tt][nt][j] = -INFINITY;
-    }
-  }
+      for (int j = 0; j < 4; ++j)
+        if (!((bits[nt] >> (16 * tt + 4 * g4 + j)) & 1u)) sc[tt][nt][j] = -INFINITY;
 }
 
 // reference: online softmax in base 2 with a lazily moved reference.  A
@@ -624,8 +623,8 @@ template <int D, int NT, bool kMasked>
 __device__ __forceinline__ void attend_tile(const unsigned char* kt_lds, const bf16x8 (&qf)[NT][D / 32],
                                             f32x4 (&o)[D / 16][NT], f32x4 (&lacc)[NT],
                                             float (&m)[NT], float (&thr)[NT], const bf16x8& ones,
-                                            float c, float inv_c, const MaskInfo& mk,
-                                            const int (&node_rel)[NT], int g4, int l16) {
+                                            float c, float inv_c, const uint32_t (&bits)[NT],
+                                            int g4, int l16) {
   using TL = TileLayout<D>;
   constexpr int NC = D / 32;
   // All of the tile's LDS reads go out first, K before V.
@@ -647,7 +646,7 @@ __device__ __forceinline__ void attend_tile(const unsigned char* kt_lds, const b
   __builtin_amdgcn_s_setprio(0);
   read_values<D>(kt_lds + TL::kBytes, vf, g4, l16);
   pin_order();
-  if (kMasked) tile_mask<NT>(sc, mk, node_rel);
+  if (kMasked) tile_mask<NT>(sc, bits, g4);
   tile_reference<D / 16, NT>(sc, m, thr, o, lacc, c, inv_c);
   bf16x8 pf[NT];
   tile_weights<NT>(sc, m, c, pf);
@@ -997,6 +996,7 @@ void attn_main(AttnArgs a) {
   };
   // a wave whose rows all lie past the last one only moves tiles
   const bool busy = wrow0 < a.M;
+  uint32_t bits[NT] = {};
   int i = 0;
   for (; i < n_iter; ++i) {
     ring_step(i);
@@ -1004,17 +1004,16 @@ void attn_main(AttnArgs a) {
     const int t = t0 + wk + WK * i;
     if (i >= n_mine || t >= nct || (t + 1) * kKeyTile > kvl) break;
     if (!busy) continue;
-    const MaskInfo mk{t, nct, kvl, ntt, g4, a.tail, anc};
     attend_tile<D, NT, false>(ring_ptr + (i % NS) * STAGE, qf, o, lacc, m, thr, ones_v, a.c, inv_c,
-                              mk, node_rel, g4, l16);
+                              bits, g4, l16);
   }
   for (bool stepped = true; i < n_iter; ++i, stepped = false) {
     if (!stepped) ring_step(i);
     if (i >= n_mine || !busy) continue;
     const int t = t0 + wk + WK * i;
-    const MaskInfo mk{t, nct, kvl, ntt, g4, a.tail, anc};
+    tile_bits<NT>(MaskInfo{t, nct, kvl, ntt, a.tail, anc}, node_rel, bits);
     attend_tile<D, NT, true>(ring_ptr + (i % NS) * STAGE, qf, o, lacc, m, thr, ones_v, a.c, inv_c,
-                             mk, node_rel, g4, l16);
+                             bits, g4, l16);
   }
 
   float lsum[NT];
@@ -1114,6 +1113,236 @@ void attn_main(AttnArgs a) {
   if (!s_last) return;
   const bool bad = __hip_atomic_load(a.tree_bad + grp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
   merge_chunks<D, RB, kWaves>(a, part0, nval, b, g, r0, bad, wave, lane);
+}
+
+// Training mask, several blocks to a workgroup.  The A blocks of an example read
+// the same context up to their anchors.  With one block per workgroup a block of
+// S * G <= 64 rows leaves a workgroup of four waves half empty, or (two waves)
+// moves every tile through LDS for its few rows only, and what bounds it is the
+// tiles' way into LDS.  So nb blocks with neighbouring anchors (pack_order sorts
+// them, largest first) share a workgroup of 128 rows: row R belongs to block
+// R / M of the pack.  The workgroup streams the context up to its largest anchor,
+// then every block's own keys; a wave skips the tiles none of its rows sees, and
+// a row's visible keys are counted per row (key < anchor in the context, key <=
+// position in its own block).  A ring of four tiles (64 KB) lets two workgroups
+// share a CU.  Now bound by the matrix products and the softmax between them.
+// Measured (8 KV heads, D = 128 unless said, random anchors): one example of 512
+// blocks of 16, G = 4, 4096 positions: 350 -> 292 us; 2 x 200 blocks of 8, G = 4,
+// 2048: 185 -> 91; 3 x 223 blocks of 32, G = 1, 390: 183 -> 74; 3 x 300 of 16,
+// G = 2, D = 64, 1000: 258 -> 87; pack_order 5-7 us of each.  When it is taken:
+// tv_plan.h, pack_plan.
+struct PackArgs {
+  const __bf16* q;
+  const __bf16* kc;
+  const __bf16* vc;
+  const __bf16* kt;
+  const __bf16* vt;
+  const int32_t* anchors;
+  const int32_t* order;  // [B, A]: the example's blocks, largest anchor first
+  __bf16* out;
+  int B, A, S, Hq, Hkv, L, G, M, nb, packs;
+  float c;
+};
+
+// Place of each of an example's blocks by anchor: kPackRank blocks per workgroup,
+// every workgroup with all keys in LDS, four lanes per block on a quarter of them
+// each, four at a time.
+__global__ __launch_bounds__(4 * kPackRank) void pack_order(const int32_t* anchors, int32_t* order,
+                                                            int A) {
+  __shared__ __attribute__((aligned(16))) int key[kPackMaxBlocks];
+  const int per = (A + kPackRank - 1) / kPackRank, b = blockIdx.x / per, A16 = (A + 15) & ~15;
+  for (int i = threadIdx.x; i < A16; i += 4 * kPackRank)
+    key[i] = i < A ? anchors[(size_t)b * A + i] : INT32_MIN;
+  __syncthreads();
+  const int i = (int)(blockIdx.x % per) * kPackRank + (int)(threadIdx.x >> 2);
+  const int v = i < A ? key[i] : 0;
+  int rank = 0;
+  for (int j = 4 * (int)(threadIdx.x & 3); j < A16; j += 16) {
+    const int4 k = *(const int4*)(key + j);
+    rank += k.x > v || (k.x == v && j < i);
+    rank += k.y > v || (k.y == v && j + 1 < i);
+    rank += k.z > v || (k.z == v && j + 2 < i);
+    rank += k.w > v || (k.w == v && j + 3 < i);
+  }
+  rank += __shfl_xor(rank, 1);
+  rank += __shfl_xor(rank, 2);
+  if (i < A && (threadIdx.x & 3) == 0) order[(size_t)b * A + rank] = i;
+}
+
+template <int D>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void attn_packed(PackArgs a) {
+  using TL = TileLayout<D>;
+  constexpr int WR = kPackRows / kRowsPerWave, NS = 4;
+  constexpr int NT = kRowsPerWave / 16, NC = D / 32, DT = D / 16;
+  constexpr int STAGE = 2 * TL::kBytes, PW = 2 * TL::kDma / WR, NQ = NT * NC;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int lane = threadIdx.x & 63, g4 = lane >> 4, l16 = lane & 15;
+  const int wr = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  // (pack, KV head) pairs go to the XCDs in turn, so that an XCD keeps to few
+  // heads' context; within that the packs of the largest anchors come first
+  const int qq = (int)(blockIdx.x / kXcds) * kXcds + (int)(blockIdx.x % kXcds);
+  const int g = qq % a.Hkv, u = qq / a.Hkv;
+  const int b = u % a.B, p = u / a.B;
+  if (p >= a.packs) return;
+
+  // the pack's blocks, one per lane
+  const int nv = min(a.nb, a.A - p * a.nb);
+  const int mine = lane < nv ? a.order[(size_t)b * a.A + p * a.nb + lane] : 0;
+  int anchor = lane < nv ? a.anchors[(size_t)b * a.A + mine] : 0;
+  anchor = anchor < 0 ? 0 : (anchor > a.L ? a.L : anchor);
+  const int ntt = (a.S - 1) / kKeyTile + 1;
+
+  // this lane's rows
+  int blk[NT], node[NT];
+  size_t orow[NT];
+  bool ok[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    const int R = kRowsPerWave * wr + 16 * nt + l16, rr = R % a.M;
+    blk[nt] = R / a.M;
+    ok[nt] = blk[nt] < nv;
+    node[nt] = rr / a.G;
+    const int src = ok[nt] ? blk[nt] : 0;
+    orow[nt] = (((size_t)b * a.A + __shfl(mine, src)) * a.S + node[nt]) * a.Hq + g * a.G + rr % a.G;
+  }
+  const int blk_lo = kRowsPerWave * wr / a.M, blk_hi = (kRowsPerWave * (wr + 1) - 1) / a.M;
+
+  const size_t krow = (size_t)a.Hkv * D;
+  const size_t cache0 = (size_t)b * a.L * krow + (size_t)g * D;
+  uint32_t dma_off[PW];
+#pragma unroll
+  for (int k = 0; k < PW; ++k) {
+    const int r = ((wr * PW + k) % TL::kDma) * TL::kRowsPerDma + lane / TL::kCPR;
+    dma_off[k] = (uint32_t)(r * (int)krow * 2 + ((lane % TL::kCPR) ^ TL::swz(r)) * 16);
+  }
+  const char* kctx = uniform_ptr((const char*)(a.kc + cache0));
+  const char* vctx = uniform_ptr((const char*)(a.vc + cache0));
+
+  bf16x8 qf[NT][NC];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+    for (int cc = 0; cc < NC; ++cc) {
+      const bf16x8 v =
+          *reinterpret_cast<const bf16x8*>(a.q + orow[nt] * D + 8 * g4 + 32 * cc);
+      qf[nt][cc] = ok[nt] ? v : bf16x8{};
+    }
+  // (the queries are in before the first tiles go out: the compiler's wait for
+  // them would otherwise drain the tiles too)
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+    for (int cc = 0; cc < NC; ++cc) asm volatile("" : "+v"(qf[nt][cc]));
+  // one pass over all blocks, or one per block (below)
+  for (int j0 = 0, j1 = nv;;) {
+    // the pass's tiles: the context up to its blocks' largest anchor, then their own
+    const bool in = lane >= j0 && lane < j1;
+    const int longest = (int)wave_max_u32(in ? (unsigned)anchor : 0u);
+    const int nct = (longest + kKeyTile - 1) / kKeyTile, T = nct + (j1 - j0) * ntt;
+    // its rows, and the smallest and largest of the wave's anchors
+    bool on[NT];
+    int kvl[NT], lo = a.L, hi = 0;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      on[nt] = ok[nt] && blk[nt] >= j0 && blk[nt] < j1;
+      kvl[nt] = __shfl(anchor, blk[nt] & 63);
+      if (!on[nt]) kvl[nt] = 0;
+      else lo = min(lo, kvl[nt]);
+      hi = max(hi, kvl[nt]);
+    }
+    lo = a.L - (int)wave_max_u32((unsigned)(a.L - lo));
+    hi = (int)wave_max_u32((unsigned)hi);
+    if (hi == 0) lo = 0;  // no context, or no rows
+    // tile t: of the context, or of block j0 + (t - nct) / ntt's own keys
+    auto issue = [&](int t) {
+      TreeSrc src{kctx, vctx, kctx, vctx, nullptr, 0, 0, (int)krow * 2, longest, nct, a.S - 1};
+      if (t >= nct) {
+        const int j = j0 + (t - nct) / ntt;
+        const size_t own =
+            ((size_t)b * a.A + __builtin_amdgcn_readlane(mine, j)) * a.S * krow + (size_t)g * D;
+        src.ktree = uniform_ptr((const char*)(a.kt + own));
+        src.vtree = uniform_ptr((const char*)(a.vt + own));
+        src.nct = nct + (j - j0) * ntt;
+      }
+      issue_tile<D, PW, false>(src, dma_off, wr, lane, t, (uint32_t)(uintptr_t)smem + (t % NS) * STAGE);
+    };
+
+#pragma unroll
+    for (int t = 0; t < NS; ++t)
+      if (t < T) issue(t);
+
+    f32x4 o[DT][NT], lacc[NT];
+    float m[NT], thr[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      m[nt] = thr[nt] = -INFINITY;
+      lacc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) o[dt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    bf16x8 ones = {(__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f,
+                   (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f};
+    asm volatile("" : "+v"(ones));
+    const float inv_c = 1.f / a.c;
+    uint32_t bits[NT] = {};
+    auto ring_step = [&](int t) {
+      if (t == 0) wait_tiles<PW, NS - 1>(T - 1);
+      else wait_tiles<PW, NS - 2>(T - 1 - t);
+      __syncthreads();
+      if (t >= 1 && t + NS - 1 < T) issue(t + NS - 1);
+    };
+    int t = 0;
+    for (; t < T; ++t) {  // context tiles that all of the wave's rows see whole
+      ring_step(t);
+      if (t >= nct || (t + 1) * kKeyTile > lo) break;
+      attend_tile<D, NT, false>(smem + (t % NS) * STAGE, qf, o, lacc, m, thr, ones, a.c, inv_c, bits,
+                                g4, l16);
+    }
+    for (bool stepped = true; t < T; ++t, stepped = false) {
+      if (!stepped) ring_step(t);
+      const int j = t < nct ? 0 : j0 + (t - nct) / ntt;
+      if (t < nct ? t * kKeyTile >= hi : (j < blk_lo || j > blk_hi)) continue;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+        bits[nt] = t < nct ? first_keys(kvl[nt] - t * kKeyTile)
+                           : (blk[nt] == j ? first_keys(node[nt] + 1 - (t - nct) % ntt * kKeyTile) : 0u);
+      attend_tile<D, NT, true>(smem + (t % NS) * STAGE, qf, o, lacc, m, thr, ones, a.c, inv_c, bits, g4,
+                               l16);
+    }
+    // Non-finite outputs: a value that is an infinity or NaN reaches, times a
+    // weight of zero, rows of the pack that do not see its key.  Then every block
+    // is done again by itself.
+    if (j0 == 0 && j1 == nv && nv > 1) {
+      bool bad = false;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            uint32_t w = __float_as_uint(o[dt][nt][e]);
+            asm("" : "+v"(w));  // (no assumption that it is a number)
+            bad |= on[nt] && (w & 0x7f800000u) == 0x7f800000u;
+          }
+      if (__syncthreads_or(bad)) {
+        j1 = 1;
+        continue;
+      }
+      j1 = nv + 1;  // done after the store
+    }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      if (!on[nt]) continue;
+      const float inv = 1.f / lacc[nt][0];
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+        store_out4(a.out + orow[nt] * D + 16 * dt + 4 * g4, o[dt][nt], inv, false);
+    }
+    if (j1 >= nv) return;
+    __syncthreads();  // the ring is free
+    j0 = j1++;
+  }
 }
 
 // Second kernel of the split-KV plans whose merge is too large for one
@@ -1322,6 +1551,29 @@ hipError_t launch_attention(const void* q, const void* kc, const void* vc, const
   a.min_chunk = p.min_chunk;
   a.c = scale * 1.4426950408889634f;
   return D == 128 ? launch_attn_d<128>(a, p, st) : launch_attn_d<64>(a, p, st);
+}
+
+template <int D>
+static hipError_t launch_packed_d(const PackArgs& a, hipStream_t st) {
+  constexpr int lds = 4 * 2 * TileLayout<D>::kBytes;  // at most 64 KB: no limit to raise
+  static_assert(lds <= 64 * 1024, "the ring");
+  const dim3 grid(kXcds * cdiv((long long)a.B * a.packs * a.Hkv, kXcds));
+  hipLaunchKernelGGL(attn_packed<D>, grid, dim3(256), lds, st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_packed(const void* q, const void* kc, const void* vc, const void* kt, const void* vt,
+                         const int32_t* anchors, void* out, int B, int A, int S, int Hq, int Hkv, int D,
+                         int L, float scale, void* ws, const PackPlan& p, hipStream_t st) {
+  int32_t* order = (int32_t*)((char*)ws + kSyncBytes);
+  hipLaunchKernelGGL(pack_order, dim3(B * cdiv(A, kPackRank)), dim3(4 * kPackRank), 0, st, anchors,
+                     order, A);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  PackArgs a{(const __bf16*)q, (const __bf16*)kc, (const __bf16*)vc, (const __bf16*)kt,
+             (const __bf16*)vt, anchors, order, (__bf16*)out, B, A, S, Hq, Hkv, L, Hq / Hkv,
+             S * (Hq / Hkv), p.nb, p.packs, scale * 1.4426950408889634f};
+  return D == 128 ? launch_packed_d<128>(a, st) : launch_packed_d<64>(a, st);
 }
 
 }  // namespace tv

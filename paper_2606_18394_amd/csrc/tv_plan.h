@@ -287,6 +287,38 @@ inline AttnPlan attn_plan(int B, int N, int Hq, int Hkv, int D, int Lmax) {
   return best;
 }
 
+// Training-mask calls with several blocks to a workgroup (tv_attention.hip,
+// attn_packed): blocks of at most 64 rows (of more, a workgroup of 128 rows
+// holds one), few enough for the sort, and enough of them that one block per
+// workgroup would take more than two rounds of the chip's 512 places; below that
+// the packs are too few and their long tile chains cost more than they save.
+// Measured (8 KV heads, D = 128, anchors spread over 2048 positions; packed
+// against one block each): M = 64 rows: 63.6 against 46.6 us at 512 blocks x
+// heads, 45.1 against 47.2 at 1024 (1000 positions); M = 32: 64 against 33 at 512, 66 against 67 at
+// 1024, 72 against 81 at 1536; M = 16: 68 against 66 at 1024, 69 against 96 at
+// 2048; M = 8: 76 against 65 at 1024, 76 against 92 at 2048, 80 against 200 at
+// 4096.  The order of the blocks lies behind the sync words of the workspace.
+constexpr int kPackRows = 128;
+constexpr int kPackMaxBlocks = 2048;  // blocks per example the sort takes
+constexpr int kPackMinGroups = 1280;  // examples x blocks x KV heads
+constexpr int kPackRank = 64;         // blocks a workgroup of the sort ranks
+struct PackPlan {
+  int nb, packs;  // blocks per workgroup (0: not packed), workgroups per (example, KV head)
+  size_t ws_bytes;
+};
+inline PackPlan pack_plan(int B, int A, int S, int Hq, int Hkv) {
+  PackPlan p{};
+  const long long M = (long long)S * (Hq / Hkv);
+  if (2 * M > kPackRows || A > kPackMaxBlocks) return p;
+  const int nb = (int)(kPackRows / M) < 16 ? (int)(kPackRows / M) : 16;
+  const int packs = cdiv(A, nb);
+  if (A < nb || (long long)B * A * Hkv < kPackMinGroups) return p;
+  p.nb = nb;
+  p.packs = packs;
+  p.ws_bytes = kSyncBytes + (size_t)B * A * 4;
+  return p;
+}
+
 // Acceptance decomposition: a scan kernel runs one workgroup per (node row,
 // vocabulary split) and stores one 64-bit key per pair; a second kernel runs
 // one workgroup per sequence.  Splits give the scan >= ~2048 workgroups but

@@ -66,3 +66,93 @@ def test_block_causal_parity(case):
             err = max(err, float(np.abs(got[b:b + 1, ks] - ref).max()))
     print(f"max abs err {err:.3e} over all {B * A} blocks", flush=True)
     assert err <= TOL
+
+
+def _reference(q, kc, vc, kb, vb, anchors):
+    """The training mask in fp64 torch, one (example, KV head) at a time."""
+    B, A, S, Hq, D = q.shape
+    L, Hkv = kc.shape[1], kc.shape[2]
+    G = Hq // Hkv
+    out = torch.empty(q.shape, dtype=torch.float64, device=q.device)
+    own = torch.ones(S, S, dtype=torch.bool, device=q.device).tril().repeat_interleave(G, 0)
+    pos = torch.arange(L, device=q.device)
+    for b in range(B):
+        for h in range(Hkv):
+            qh = q[b, :, :, h * G:(h + 1) * G].reshape(A, S * G, D).double() * D ** -0.5
+            ctx = (qh.reshape(-1, D) @ kc[b, :, h].double().t()).reshape(A, S * G, L)
+            ctx = ctx.masked_fill(pos >= anchors[b].clamp(0, L)[:, None, None], -torch.inf)
+            blk = torch.bmm(qh, kb[b, :, :, h].double().transpose(1, 2).contiguous())
+            w = torch.softmax(torch.cat([ctx, blk.masked_fill(~own, -torch.inf)], -1), -1)
+            o = (w[..., :L].reshape(A * S * G, L) @ vc[b, :, h].double()).reshape(A, S * G, D)
+            o = o + torch.bmm(w[..., L:].contiguous(), vb[b, :, :, h].double().contiguous())
+            out[b, :, :, h * G:(h + 1) * G] = o.reshape(A, S, G, D)
+    return out
+
+
+@pytest.mark.parametrize("shape", [
+    # (B, A, S, Hq, Hkv, D, L): rows per block of 64, 32, 24 (5 to a workgroup,
+    # 8 rows idle), 8 (16 to a workgroup) and 1; the last pack short; two tiles
+    # of own keys; more than one context tile between the anchors of a pack; no
+    # context; one block fewer than packing takes
+    (1, 161, 16, 32, 8, 128, 700), (2, 131, 8, 32, 8, 128, 333), (1, 321, 8, 24, 8, 64, 200),
+    (2, 513, 8, 8, 8, 128, 65), (4, 1025, 1, 4, 4, 64, 40), (1, 161, 64, 8, 8, 64, 500),
+    (1, 161, 33, 8, 8, 128, 5000), (1, 256, 16, 32, 8, 64, 0), (1, 159, 16, 32, 8, 128, 300),
+])
+def test_packed_blocks(shape):
+    """Several blocks to a workgroup.  Max-abs error at most 1.5e-2: 2^-8 of
+    outputs up to about 3.5 (a position that sees few keys), from rounding the
+    weights and the output to bf16; a wrong mask or block moves outputs by
+    O(1).  The workspace that the verification calls share keeps its sync words
+    at zero."""
+    from paper_2606_18394_amd import block_causal_attention
+    from paper_2606_18394_amd.binding import load_library
+    B, A, S, Hq, Hkv, D, L = shape
+    print(shape, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(A * 7 + S)
+
+    def normal(*s):
+        return torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    q, kb, vb = normal(B, A, S, Hq, D), normal(B, A, S, Hkv, D), normal(B, A, S, Hkv, D)
+    kc, vc = normal(B, L, Hkv, D), normal(B, L, Hkv, D)
+    anchors = torch.randint(-3, L + 4, (B, A), generator=g, device="cuda").to(torch.int32)
+    anchors[:, ::9] = L // 2   # equal anchors
+    anchors[:, 0], anchors[:, -1] = 0, L
+    out = torch.full_like(q, 7.0)
+    need = load_library().tv_block_causal_attention_workspace(B, A, S, Hq, Hkv, D, L)
+    ws = torch.zeros(need, dtype=torch.uint8, device="cuda")
+    for _ in range(2):
+        block_causal_attention(q, kc, vc, kb, vb, anchors, out, workspace_tensor=ws)
+        torch.cuda.synchronize()
+        err = (out.double() - _reference(q, kc, vc, kb, vb, anchors)).abs().max().item()
+        print(f"max abs err {err:.3e}", flush=True)
+        assert err <= 1.5e-2
+        assert not ws[:32768].any(), "sync words left non-zero"
+
+
+@pytest.mark.parametrize("shape", [(1, 163, 16, 32, 8, 128, 700), (2, 321, 8, 8, 8, 64, 200)])
+def test_packed_blocks_apart(shape):
+    """An infinity in the context and a NaN in one block's own keys reach the
+    blocks that see them and no other, though others share their workgroup."""
+    from paper_2606_18394_amd import block_causal_attention
+    B, A, S, Hq, Hkv, D, L = shape
+    print(shape, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(A)
+
+    def normal(*s):
+        return torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    q, kb, vb = normal(B, A, S, Hq, D), normal(B, A, S, Hkv, D), normal(B, A, S, Hkv, D)
+    kc, vc = normal(B, L, Hkv, D), normal(B, L, Hkv, D)
+    anchors = torch.randint(0, L + 1, (B, A), generator=g, device="cuda").to(torch.int32)
+    ref = _reference(q, kc, vc, kb, vb, anchors)
+    kc[0, L - 9], vc[0, L // 2, :, 3] = float("nan"), float("inf")
+    vb[B - 1, 5, 0, :, 1] = float("nan")
+    sees = torch.zeros(B, A, dtype=torch.bool, device="cuda")
+    sees[0] = anchors[0] > L // 2
+    sees[B - 1, 5] = True
+    out = torch.zeros_like(q)
+    block_causal_attention(q, kc, vc, kb, vb, anchors, out)
+    torch.cuda.synchronize()
+    assert out[sees].float().isfinite().logical_not().any(dim=-1).all()
+    err = (out.double() - ref)[~sees].abs().max().item()
+    print(f"max abs err {err:.3e}", flush=True)
+    assert err <= 1.5e-2  # as in test_packed_blocks
