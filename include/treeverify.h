@@ -157,8 +157,8 @@ int tv_tree_verify_attention_paged(const void* q, const void* k_pool, const void
  *
  * Scale, precision, GQA mapping and requirements as in
  * tv_tree_verify_attention with B*A sequences of S nodes (S <= TV_MAX_NODES,
- * B*A <= 2^24); it runs on the same kernels, each block as a chain tree whose
- * cache is its example's context cut at its anchor.  The workspace is
+ * B*A <= 2^24): each block is a chain tree whose cache is its example's
+ * context cut at its anchor.  The workspace is
  * tv_block_causal_attention_workspace(B, A, S, Hq, Hkv, D, L) bytes,
  * zero-filled before first use like the verification workspace.  Forward
  * only.

@@ -186,8 +186,9 @@ int tv_block_causal_attention(const void* q, const void* k_ctx, const void* v_ct
     return TV_ERR_ALIGN;
   if (!(scale > 0.f)) scale = 1.0f / sqrtf((float)D);
   const tv::PackPlan pk = tv::pack_plan(B, A, S, Hq, Hkv);
-  if (pk.nb > 0) {
-    if (!workspace || workspace_bytes < pk.ws_bytes) return TV_ERR_WORKSPACE;
+  // (a smaller workspace, or none, is enough for one block per workgroup
+  // where that plan does not split)
+  if (pk.nb > 0 && workspace && workspace_bytes >= pk.ws_bytes) {
     if (misaligned(workspace)) return TV_ERR_ALIGN;
     const hipError_t e = tv::launch_packed(q, k_ctx, v_ctx, k_blk, v_blk, anchors, out, B, A, S, Hq,
                                            Hkv, D, L, scale, workspace, pk, stream);

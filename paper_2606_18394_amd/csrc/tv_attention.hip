@@ -11,8 +11,11 @@
 // (node, head-in-group) pairs, row r = node * G + head.  Keys are cut into
 // 32-key tiles: ceil(kv_len/32) cache tiles, then the tree tiles up to the
 // last node of the row block (a node never sees a later node because
-// parents precede children).  The tiles are cut into S contiguous chunks of
-// a fixed size (split-KV).  A workgroup takes one block of 32*WR rows and
+// parents precede children).  The tiles are cut into contiguous chunks
+// (split-KV) of one size for the whole batch, found on the device from the
+// kv_lens (even_split), so that a capacity far above the lengths or a ragged
+// batch still gives chunks of like size; a sequence of one chunk is written
+// straight to the output.  A workgroup takes one block of 32*WR rows and
 // one chunk with WR x WK wave64s: WR row groups of 32 rows, and WK key
 // groups that share out the chunk's tiles, each streaming its tiles through
 // an LDS ring of NS stages; key groups merge their softmax states in LDS at
@@ -32,11 +35,12 @@
 // the S^T accumulators (the 32 keys are ordered so the B operand needs no
 // data movement) and V^T from ds_read_b64_tr_b16 transposing reads.
 //
-// Split-KV merge (S > 1).  Every chunk stores its (max, sum, O) partial.
-// When one workgroup can merge a row block with at most two batches of
-// loads, the chunk that finishes last does it inside this kernel (arrival
-// counters in the workspace); otherwise a second kernel merges all row
-// blocks.
+// Split-KV merge (sequences of several chunks).  Every chunk stores its (max,
+// sum, O) partial.  The chunk that finishes last merges its row block inside
+// this kernel (arrival counters in the workspace) when the plan prices that
+// below a second kernel that merges all row blocks.
+//
+// The training mask of many small blocks has a kernel of its own (attn_packed).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>

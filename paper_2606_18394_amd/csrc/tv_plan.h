@@ -136,7 +136,8 @@ inline AttnPlan attn_plan_arr(int B, int N, int Hq, int Hkv, int D, int Lmax, in
   // each XCD whole sequences and very different work, so each XCD instead
   // takes one KV head and one of L = 8/Hkv lanes of chunks: chunk s of
   // sequence b goes to lane (b + s) % L.  Every XCD then sees every
-  // sequence.  This needs Hkv to divide 8 and L to divide S.
+  // sequence.  This needs Hkv to divide 8 and L to divide S.  (Plans with
+  // an even split map their workgroups by its chunks instead.)
   p.spread = p.slots == 0 && B > 1 && kXcds % Hkv == 0 && p.S % (kXcds / Hkv) == 0;
   // Within an XCD workgroups start in index order as slots free up, so a
   // long chunk that starts in a late round sets the kernel's end.  When an

@@ -156,3 +156,26 @@ def test_packed_blocks_apart(shape):
     err = (out.double() - ref)[~sees].abs().max().item()
     print(f"max abs err {err:.3e}", flush=True)
     assert err <= 1.5e-2  # as in test_packed_blocks
+
+
+@pytest.mark.parametrize("size", [256, 32768 + 4 * 163 - 1])
+def test_packed_blocks_small_workspace(size):
+    """Less workspace than the query asks for, where one block per workgroup
+    needs none: accepted, and computed that way."""
+    from paper_2606_18394_amd import block_causal_attention
+    B, A, S, Hq, Hkv, D, L = 1, 163, 16, 32, 8, 128, 300
+    g = torch.Generator(device="cuda").manual_seed(size)
+
+    def normal(*s):
+        return torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    q, kb, vb = normal(B, A, S, Hq, D), normal(B, A, S, Hkv, D), normal(B, A, S, Hkv, D)
+    kc, vc = normal(B, L, Hkv, D), normal(B, L, Hkv, D)
+    anchors = torch.randint(0, L + 1, (B, A), generator=g, device="cuda").to(torch.int32)
+    out = torch.full_like(q, 7.0)
+    ws = torch.zeros(size, dtype=torch.uint8, device="cuda")
+    block_causal_attention(q, kc, vc, kb, vb, anchors, out, workspace_tensor=ws)
+    torch.cuda.synchronize()
+    err = (out.double() - _reference(q, kc, vc, kb, vb, anchors)).abs().max().item()
+    print(f"max abs err {err:.3e}", flush=True)
+    assert err <= 1.5e-2  # as in test_packed_blocks
+    assert not ws.any()
