@@ -114,7 +114,7 @@ KERNEL_PATTERNS = {
     # (template arguments D, WR, WK, NS, paged, shared queries)
     "attn_main": (r"attn_main<(\d+), (\d+), (\d+), (\d+), false(?:, (?:false|true))?>",
                   "attn_main<%s,%s,%s,%s>"),
-    "accept_scan": (r"accept_scan<(\w+), (\w+)>", "accept_scan<%s,%s>"),
+    "accept_scan": (r"accept_scan<(\w+)>", "accept_scan<%s>"),
 }
 
 
