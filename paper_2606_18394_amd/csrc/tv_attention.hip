@@ -75,6 +75,7 @@ struct AttnArgs {
   int B, N, Hq, Hkv, Lmax, G, M, nRB, S, chunk, nwork;
   int fused;   // split-KV merge inside the main kernel (else a second kernel)
   int slots, min_chunk;  // even split (tv_plan.h): chunks per (KV head, row block), else 0
+  float rslots, rslack;  // 1 / slots, 1 / (slots - B)
   int spread;  // work order of several sequences (tv_plan.h, work_item)
   float c;  // scale * log2(e): scores live in base-2 exponent units
   const int32_t* block_table;  // paged cache: [B, max_blocks], else NULL
@@ -83,28 +84,28 @@ struct AttnArgs {
   int cgroup;  // sequences sharing one cache (sequence b reads cache b / cgroup)
 };
 
-// The keys a sequence's row block attends over.  Separate tree K/V: nct
-// cache tiles (rows < kvl) then the tree tiles of nodes 0..i_hi.  Tree-tail
-// layout: the tree rows follow the context in the cache (kvl is clamped to
-// Lmax - N so they fit) and one run of nct = T tiles covers rows
-// 0 .. kvl + i_hi.  A NULL kv_len means full caches.
-struct Segment {
-  int kvl, nct, T;
-};
-__device__ __forceinline__ Segment segment(const AttnArgs& a, int b, int i_hi) {
+// Context rows of sequence b: its kv_len clamped to what the cache holds (in
+// the tree-tail layout behind room for the tree); a NULL kv_len means full.
+__device__ __forceinline__ int context_rows(const AttnArgs& a, int b) {
   const int cap = a.tail ? a.Lmax - a.N : a.Lmax;
-  int kvl = a.kv_len ? a.kv_len[b] : cap;
-  kvl = kvl < 0 ? 0 : (kvl > cap ? cap : kvl);
-  Segment sg;
-  sg.kvl = kvl;
+  const int kvl = a.kv_len ? a.kv_len[b] : cap;
+  return kvl < 0 ? 0 : (kvl > cap ? cap : kvl);
+}
+
+// The key tiles a row block attends over, behind kvl context rows and up to
+// node i_hi.  Separate tree K/V: nct cache tiles (rows < kvl) then the tree
+// tiles of nodes 0..i_hi.  Tree-tail layout: the tree rows follow the context
+// in the cache and one run of nct = T tiles covers rows 0 .. kvl + i_hi.
+struct Segment {
+  int nct, T;
+};
+__device__ __forceinline__ Segment segment(const AttnArgs& a, int kvl, int i_hi) {
   if (a.tail) {
-    sg.nct = (kvl + i_hi + kKeyTile) / kKeyTile;
-    sg.T = sg.nct;
-  } else {
-    sg.nct = (kvl + kKeyTile - 1) / kKeyTile;
-    sg.T = sg.nct + i_hi / kKeyTile + 1;
+    const int t = (kvl + i_hi + kKeyTile) / kKeyTile;
+    return Segment{t, t};
   }
-  return sg;
+  const int nct = (kvl + kKeyTile - 1) / kKeyTile;
+  return Segment{nct, nct + i_hi / kKeyTile + 1};
 }
 
 // Longest-first order of a ragged batch (spread = 2).  XCD x serves one KV
@@ -121,26 +122,28 @@ constexpr int kRankPerLane = 16;  // == kMaxRankPairs / 64 in tv_plan.h
 
 __device__ __forceinline__ void longest_first(const AttnArgs& a, int bid, WorkItem& it) {
   const int lane = threadIdx.x & 63;
-  const int L = kXcds / a.Hkv, per_b = a.S / L, npairs = a.B * per_b;
+  const int L = kXcds / a.Hkv, per_b = a.S / L, npairs = a.B * per_b;  // L: a power of two
   const int x = bid % kXcds, target = (bid / kXcds) / a.nRB, ln = x / a.Hkv;
-  const int cap = a.tail ? a.Lmax - a.N : a.Lmax;
+  const int nk = (npairs + 63) / 64;  // pair slots in use per lane
+  // pair p's sequence (p < 2^10: the reciprocal is exact enough), and its chunk
+  const float rper = __builtin_amdgcn_rcpf((float)per_b);
+  auto seq = [&](int p) { return (int)(((float)p + 0.5f) * rper); };
+  auto chunk_of = [&](int p, int b) { return ((ln - b) & (L - 1)) + L * (p - b * per_b); };
   int key[kRankPerLane];
+  // all lengths are requested before any is used
+#pragma unroll
+  for (int k = 0; k < kRankPerLane; ++k)
+    key[k] = k < nk ? context_rows(a, seq(min(lane + 64 * k, npairs - 1))) : -1;
 #pragma unroll
   for (int k = 0; k < kRankPerLane; ++k) {
     const int p = lane + 64 * k;
-    key[k] = -1;
-    if (p < npairs) {
-      const int pb = p / per_b;
-      const int ps = ((ln - pb) % L + L) % L + L * (p % per_b);
-      int kvl = a.kv_len ? a.kv_len[pb] : cap;
-      kvl = kvl < 0 ? 0 : (kvl > cap ? cap : kvl);
-      const int tiles = (kvl + kKeyTile - 1) / kKeyTile + (a.N - 1) / kKeyTile + 1;
-      const int work = max(0, min(a.chunk, tiles - ps * a.chunk));  // < 2^14 (plan)
-      key[k] = (work << 16) | (0xFFFF - p);
+    if (k < nk) {
+      const int tiles = (key[k] + kKeyTile - 1) / kKeyTile + (a.N - 1) / kKeyTile + 1;
+      const int work = max(0, min(a.chunk, tiles - chunk_of(p, seq(p)) * a.chunk));  // < 2^14 (plan)
+      key[k] = p < npairs ? (work << 16) | (0xFFFF - p) : -1;
     }
   }
   int p;
-  const int nk = (npairs + 63) / 64;  // pair slots in use per lane
   if (nk == 1) {
     // one pair per lane: every lane counts the larger keys by lane exchanges
     int rank = 0;
@@ -148,31 +151,26 @@ __device__ __forceinline__ void longest_first(const AttnArgs& a, int bid, WorkIt
     const unsigned long long hit = __ballot(lane < npairs && rank == target);
     p = __builtin_amdgcn_readfirstlane(hit ? (int)__builtin_ctzll(hit) : 0);
   } else {
-    // the largest v with at least target + 1 keys >= v is the wanted key
+    // the largest v with at least target + 1 keys >= v is the wanted key (unused
+    // slots count for none; four at a time, since a branch over each costs more
+    // than it skips)
     int lo = 0, hi = 1 << 30;
     while (hi - lo > 1) {
       const int mid = lo + ((hi - lo) >> 1);
       int c = 0;
 #pragma unroll
-      for (int k = 0; k < kRankPerLane; ++k)
-        if (k < nk) c += __popcll(__ballot(key[k] >= mid));
+      for (int k4 = 0; k4 < kRankPerLane; k4 += 4) {
+        if (k4 >= nk) break;
+#pragma unroll
+        for (int k = k4; k < k4 + 4; ++k) c += __popcll(__ballot(key[k] >= mid));
+      }
       if (c >= target + 1) lo = mid;
       else hi = mid;
     }
     p = 0xFFFF - (lo & 0xFFFF);
   }
-  it.b = p / per_b;
-  it.s = ((ln - it.b) % L + L) % L + L * (p % per_b);
-}
-
-// Tiles of sequence b for its last row block (the chunk sizes must not depend
-// on the row block: a chunk's row blocks read the same keys).
-__device__ __forceinline__ int sequence_tiles(const AttnArgs& a, int b) {
-  const int cap = a.tail ? a.Lmax - a.N : a.Lmax;
-  int kvl = a.kv_len ? a.kv_len[b] : cap;
-  kvl = kvl < 0 ? 0 : (kvl > cap ? cap : kvl);
-  return a.tail ? (kvl + a.N + kKeyTile - 1) / kKeyTile
-                : (kvl + kKeyTile - 1) / kKeyTile + (a.N - 1) / kKeyTile + 1;
+  it.b = seq(p);
+  it.s = chunk_of(p, it.b);
 }
 
 __device__ __forceinline__ int wave_sum(int x) {
@@ -184,51 +182,82 @@ __device__ __forceinline__ int wave_sum(int x) {
          __builtin_amdgcn_readlane(x, 32) + __builtin_amdgcn_readlane(x, 48);
 }
 
-// ceil(x / c) for 1 <= x, c < 2^20: the quotient's distance to the next whole
-// number below, at least 1 / (2 c), is far above the reciprocal's error
+// Sums over the lanes up to each one (shifts by 1, 2, 4 and 8 lanes inside a
+// row of 16, then row 0's and row 2's last lane into the next row and lane 31
+// into rows 2 and 3), without the LDS crossbar.
+__device__ __forceinline__ int wave_scan(int x) {
+  x += (int)dpp_u32<0x111>((unsigned)x);
+  x += (int)dpp_u32<0x112>((unsigned)x);
+  x += (int)dpp_u32<0x114>((unsigned)x);
+  x += (int)dpp_u32<0x118>((unsigned)x);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);
+  return x;
+}
+
+// ceil(x / c) for 0 <= x < 2^20, 1 <= c < 2^20, rc = 1 / c to one ulp: the
+// quotient's distance to the next whole number below, at least 1 / (2 c), is
+// above the errors of the reciprocal and the product (together 1.5 * 2^-23 of a
+// quotient of at most (x + c) / c)
 __device__ __forceinline__ int ceil_div(int x, int c, float rc) {
   return (int)(((float)(x + c) - 0.5f) * rc);
 }
 
-// Even split of the batch (a.slots > 0): one chunk size for all sequences,
-// the smallest for which they need at most a.slots chunks together.  Found
-// from the kv_lens by every wave alike (one sequence per lane, bisection on
-// the chunk size with wave-wide sums), in a few hundred cycles; B = 1 needs
-// one division.  `first` is the lane's sequence's first chunk in the order of
-// the sequences and `count` the number of chunks in all.
-struct EvenSplit {
-  int chunk, first, count;
+// Even split of the batch (a.slots > 0): one chunk size for all sequences, the
+// smallest for which they need at most a.slots chunks together.  Every wave
+// finds it alike from the kv_lens, and with it the sequence b and the chunk s of
+// it that a work item is (s < 0: past the work), the number `first` of that
+// sequence's first chunk and its context rows kvl.  All of it comes before a
+// workgroup's first load of keys, so it is kept short: a whole division is some
+// 40 instructions and another look at kv_len a round trip to the cache, so the
+// quotients are taken with reciprocals (the host's where the divisor is its) and
+// kvl comes out of the lane that holds it.  (With whole divisions, a scan over the
+// LDS crossbar and kv_len read twice: 33 nodes x 16 sequences of 300 to 4096 rows
+// 54.7 us, now 53.6; 2 x 24 nodes over 4360 rows 18.5, now 17.7; 37 x 4 nodes over
+// 271 rows 13.7, now 13.1; 64 nodes over 4096 rows 20.0, now 19.9.)
+struct EvenItem {
+  int chunk, b, s, first, kvl;
 };
-__device__ __forceinline__ EvenSplit even_split(const AttnArgs& a) {
+
+// One sequence: the item's number is the chunk's.
+__device__ __forceinline__ EvenItem even_one(const AttnArgs& a, int item) {
+  const int kvl = context_rows(a, 0);
+  const int t = segment(a, kvl, a.N - 1).T;
+  const int chunk = max(a.min_chunk, ceil_div(t, a.slots, a.rslots));
+  return EvenItem{chunk, 0, item * chunk < t ? item : -1, 0, kvl};
+}
+
+// Several, one per lane.  The tiles are those of the last row block: a chunk's
+// row blocks read the same keys.  With item < 0 it is sequence b that is looked
+// up (its s is then of no use).
+__device__ __forceinline__ EvenItem even_lanes(const AttnArgs& a, int item, int b) {
   const int lane = threadIdx.x & 63;
-  if (a.B == 1) {
-    const int t = sequence_tiles(a, 0);
-    const int chunk = max(a.min_chunk, (t + a.slots - 1) / a.slots);
-    return EvenSplit{chunk, 0, (t + chunk - 1) / chunk};
-  }
-  const int t = lane < a.B ? sequence_tiles(a, lane) : 0;
-  const int total = wave_sum(t), longest = (int)wave_max_u32((unsigned)t);
-  // below lo the chunks are too small or too many; at hi they are few enough:
-  // the sum of ceil(t / hi) is below total / hi + B
-  int lo = max(a.min_chunk, (total + a.slots - 1) / a.slots) - 1;
-  int hi = a.slots > a.B ? min(longest, (total + a.slots - a.B - 1) / (a.slots - a.B)) : longest;
-  hi = max(hi, lo + 1);
-  auto chunks = [&](int c) {
-    return lane < a.B ? ceil_div(t, c, __builtin_amdgcn_rcpf((float)c)) : 0;
-  };
+  const int kvl = context_rows(a, min(lane, a.B - 1));
+  const int t = lane < a.B ? segment(a, kvl, a.N - 1).T : 0;
+  const float total = (float)wave_sum(t);
+  const int longest = (int)wave_max_u32((unsigned)t);
+  // Chunks of less than total / slots tiles are too many, those of total /
+  // (slots - B) few enough (the sum of ceil(t / c) is below total / c + B); the
+  // margins cover the rounding.
+  int lo = max(a.min_chunk - 1, (int)(total * a.rslots * 0.999999f) - 1);
+  int hi = max(min(longest, (int)(total * a.rslack * 1.000001f) + 1), lo + 1);
+  auto chunks = [&](int c) { return ceil_div(t, c, __builtin_amdgcn_rcpf((float)c)); };
   while (hi - lo > 1) {
     const int mid = lo + ((hi - lo) >> 1);
     if (wave_sum(chunks(mid)) <= a.slots) hi = mid;
     else lo = mid;
   }
-  const int n = chunks(hi);
-  int incl = n;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(incl, o);
-    if (lane >= o) incl += y;
-  }
-  return EvenSplit{hi, incl - n, __builtin_amdgcn_readlane(incl, 63)};
+  const int n = chunks(hi), upto = wave_scan(n);
+  // the last sequence that starts at or before the item
+  if (item >= 0) b = __popcll(__ballot(lane < a.B && upto - n <= item)) - 1;
+  const int first = __builtin_amdgcn_readlane(upto - n, b);
+  return EvenItem{hi, b, item < __builtin_amdgcn_readlane(upto, 63) ? item - first : -1, first,
+                  __builtin_amdgcn_readlane(kvl, b)};
+}
+
+// Work item `item` of the batch, or (item < 0) what concerns sequence b.
+__device__ __forceinline__ EvenItem even_split(const AttnArgs& a, int item, int b) {
+  return a.B == 1 ? even_one(a, item) : even_lanes(a, item, b);
 }
 
 // Four output values, or four NaN when the sequence's tree is invalid (the
@@ -752,19 +781,21 @@ void attn_main(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
   WorkItem it{};
-  int chunk = a.chunk, part0;  // part0: the row block's first chunk partial
+  int chunk = a.chunk, kvl, part0;  // part0: the row block's first chunk partial
   if (a.slots > 0) {
-    const EvenSplit ev = even_split(a);
-    chunk = ev.chunk;
-    const int item = even_item(blockIdx.x, ev.count, a.nRB, a.Hkv, it);
+    const int item = even_item(blockIdx.x, a.slots, a.nRB, a.Hkv, it);
     if (item < 0) return;
-    // the last sequence that starts at or before the item
-    it.b = a.B == 1 ? 0 : __popcll(__ballot((int)(threadIdx.x & 63) < a.B && ev.first <= item)) - 1;
-    it.s = item - (a.B == 1 ? 0 : __builtin_amdgcn_readlane(ev.first, it.b));
-    part0 = (it.g * a.nRB + it.rb) * a.slots + item - it.s;
+    const EvenItem ev = even_split(a, item, 0);
+    if (ev.s < 0) return;
+    it.b = ev.b;
+    it.s = ev.s;
+    chunk = ev.chunk;
+    kvl = ev.kvl;
+    part0 = (it.g * a.nRB + it.rb) * a.slots + ev.first;
   } else {
     if (!work_item(gridDim.x, a.nwork, a.S, a.nRB, a.spread, a.B, a.Hkv, blockIdx.x, it)) return;
     if (a.spread == 2) longest_first(a, blockIdx.x, it);
+    kvl = context_rows(a, it.b);
     part0 = ((it.b * a.Hkv + it.g) * a.nRB + it.rb) * a.S;
   }
   const int s = it.s, rb = it.rb, g = it.g, b = it.b;
@@ -776,8 +807,8 @@ void attn_main(AttnArgs a) {
   const int r0 = rb * RB;
   const int rows = min(RB, a.M - r0);
   const int i_lo = r0 / a.G, i_hi = (r0 + rows - 1) / a.G;
-  const Segment sg = segment(a, b, i_hi);
-  const int kvl = sg.kvl, nct = sg.nct, T = sg.T;
+  const Segment sg = segment(a, kvl, i_hi);
+  const int nct = sg.nct, T = sg.T;
   const int ntt = i_hi / kKeyTile + 1;  // words of a node's ancestor bitmask
   const int t0 = s * chunk;
   const int t1 = min(T, t0 + chunk);
@@ -1381,18 +1412,14 @@ __global__ __launch_bounds__(256) void attn_combine(AttnArgs a) {
   // chunks of this row block that hold tiles (the same count the main
   // kernel derives from kv_len and the block's last node)
   const int i_hi = (min(rb * RB + RB, a.M) - 1) / a.G;
-  int chunk = a.chunk, nslot = a.S;
-  size_t base = (size_t)(bg * a.nRB + rb) * a.S;  // first chunk partial
+  // the first chunk partial, and the partials from there on
+  EvenItem ev{a.chunk, b, 0, 0, 0};
+  size_t base = (size_t)(bg * a.nRB + rb) * a.S;
+  int nslot = a.S;
   if (a.slots > 0) {
-    nslot = a.slots;
-    base = (size_t)(g * a.nRB + rb) * a.slots;
-    if (a.B > 1) {
-      const EvenSplit ev = even_split(a);
-      chunk = ev.chunk;
-      const int first = __builtin_amdgcn_readlane(ev.first, b);
-      base += first;
-      nslot -= first;
-    }
+    if (a.B > 1) ev = even_split(a, -1, b);
+    base = (size_t)(g * a.nRB + rb) * a.slots + ev.first;
+    nslot = a.slots - ev.first;
   }
   float2 ml0[U];
   f32x4 ov0[U];
@@ -1402,9 +1429,10 @@ __global__ __launch_bounds__(256) void attn_combine(AttnArgs a) {
       ml0[u] = a.ws_ml[(base + u) * RB + row];
       ov0[u] = a.ws_o[((base + u) * DT * NTG + dt * NTG + ntg) * 64 + lane];
     }
-  const int T = segment(a, b, i_hi).T;
-  if (a.slots > 0 && a.B == 1) chunk = even_split(a).chunk;
-  const int nval = (T + chunk - 1) / chunk;
+  if (a.slots == 0) ev.kvl = context_rows(a, b);
+  else if (a.B == 1) ev = even_one(a, 0);
+  const int T = segment(a, ev.kvl, i_hi).T;
+  const int nval = (T + ev.chunk - 1) / ev.chunk;
   if (nval == 1) return;  // written by its only chunk
   float m = -INFINITY, l = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -1553,6 +1581,8 @@ hipError_t launch_attention(const void* q, const void* kc, const void* vc, const
   a.spread = p.spread;
   a.slots = p.slots;
   a.min_chunk = p.min_chunk;
+  a.rslots = p.slots > 0 ? 1.f / (float)p.slots : 0.f;
+  a.rslack = p.slots > B ? 1.f / (float)(p.slots - B) : 1.f;
   a.c = scale * 1.4426950408889634f;
   return D == 128 ? launch_attn_d<128>(a, p, st) : launch_attn_d<64>(a, p, st);
 }
