@@ -90,3 +90,35 @@ def test_lengths(shape, kind):
                                 par, out, kv_len=kvl)
     torch.cuda.synchronize()
     assert np.abs(out.float().cpu().numpy() - ref).max() <= 1.5e-2
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [
+    # (B, N, Hq, Hkv, D, rows): 1 to 16 rows per KV head, merged by the last chunk
+    # and by a second kernel
+    (1, 1, 2, 2, 128, 4000), (1, 4, 4, 1, 64, 3000), (1, 2, 64, 8, 128, 30000), (2, 1, 1, 1, 128, 9000),
+])
+def test_partials_hold_the_rows_only(shape):
+    """At most 16 rows per KV head, in row blocks of at least 32: no more than
+    half of the workspace's partials are written."""
+    import torch
+    from paper_2606_18394_amd import tree_verify_attention
+    from paper_2606_18394_amd.binding import load_library
+    B, N, Hq, Hkv, D, L = shape
+    print(shape, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(N)
+
+    def normal(*s):
+        return torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    q, kc, vc = normal(B, N, Hq, D), normal(B, L, Hkv, D), normal(B, L, Hkv, D)
+    kt, vt = normal(B, N, Hkv, D), normal(B, N, Hkv, D)
+    par = torch.arange(-1, N - 1, dtype=torch.int32, device="cuda").repeat(B, 1)
+    need = load_library().tv_tree_verify_attention_workspace(B, N, Hq, Hkv, D, L)
+    assert need > 32768, "the plan does not split"
+    ws = torch.full((need,), 0xA5, dtype=torch.uint8, device="cuda")
+    ws[:32768] = 0
+    tree_verify_attention(q, kc, vc, kt, vt, par, torch.empty_like(q), workspace_tensor=ws)
+    torch.cuda.synchronize()
+    written = int((ws[32768:] != 0xA5).sum())
+    print(f"{written} of {need - 32768} bytes", flush=True)
+    assert 0 < written <= (need - 32768) // 2
