@@ -202,14 +202,15 @@ inline bool attn_plan_fits(const AttnPlan& p) {
 // Relative time of a plan, roughly in microseconds.  The constants are fitted so
 // that the plan picked is the fastest measured one: 260 shapes (1 to 32
 // sequences, 8 to 512 nodes, 256 to 32768 cached rows, the head shapes of the
-// models above and D = 64) in every arrangement and up to four split counts; the
-// plans picked are 3.3% slower than the fastest on average.  A chunk's tiles take
-// their turns at one time per tile and key group: the latency of a tile's chain
-// of LDS reads, matrix and vector work, or the CU's share of that work.  A
-// chunk's row blocks all run on one XCD, so what does not fit the XCDs at once
-// queues there.  On top come the fixed costs at a workgroup's two ends, HBM as
-// the floor of the streaming, and the split's partials.  The lengths of several
-// sequences are unknown here: they are taken as spread over the capacity,
+// models above and D = 64) in every arrangement and up to four split counts, and
+// for the merges 170 more (1 to 64 sequences, 1 to 2000 nodes, 1 to 32 KV heads,
+// up to 130000 rows).  A chunk's tiles take their turns at one time per tile and
+// key group: the latency of a tile's chain of LDS reads, matrix and vector work,
+// or the CU's share of that work.  A split plan's chunk has all its row blocks on
+// one XCD, so what does not fit the XCDs at once queues there.  On top come the
+// fixed costs at a workgroup's two ends, HBM as the floor of the streaming (also
+// at what the CUs at work can ask for), and the split's partials.  The lengths of
+// several sequences are unknown here: they are taken as spread over the capacity,
 // kMeanFill of it on average.
 constexpr double kMeanFill = 0.64;
 
@@ -217,6 +218,10 @@ constexpr double kMeanFill = 0.64;
 // (its latency alone: 1.15, with two ring stages 1.28).
 constexpr double kTileFull[] = {1.60, 1.24, 1.33, 1.41, 1.15, 1.28, 1.32};
 static_assert(sizeof(kTileFull) / sizeof(kTileFull[0]) == kNumArrangements, "one per arrangement");
+
+// Bytes per microsecond one CU can ask HBM for.  2 sequences of 80754 rows, 4
+// nodes, 8 KV heads, D = 64: 128 workgroups of 8 waves 95 us, 256 75.
+constexpr double kCuBytes = 75.0e3;
 
 inline double attn_plan_cost(AttnPlan& p, int B, int Hkv, int D, int Lmax, int N) {
   const double longest = cdiv(Lmax, kKeyTile) + cdiv(N, kKeyTile);
@@ -238,26 +243,51 @@ inline double attn_plan_cost(AttnPlan& p, int B, int Hkv, int D, int Lmax, int N
   if (kTileFull[p.arr] * waves / 8.0 > tile) tile = kTileFull[p.arr] * waves / 8.0;
   if (D == 64) tile *= 0.55;
   double t = chunk / p.WK * tile;
-  const double per_xcd = (double)cdiv((long long)(items * Hkv + 0.999), kXcds) * p.nRB;
-  const long long rounds = cdiv((long long)per_xcd, 32LL * p.wg_per_cu);
+  // workgroups of the fullest XCD over what it holds at once (unsplit plans
+  // spread their row blocks over all XCDs)
+  const long long per_xcd = (long long)cdiv((long long)(items * Hkv + 0.999), kXcds) * p.nRB;
+  const long long rounds = p.slots > 0 ? cdiv(per_xcd, 32LL * p.wg_per_cu)
+                                       : cdiv((long long)wgs, (long long)room);
   if (rounds > 1) {
-    const double queue = B * mean * Hkv * p.nRB / room / p.WK * tile + 0.34 * t;
+    double load = B * mean * Hkv * p.nRB / room;  // tiles a place takes, on average
+    const double fullest = per_xcd * chunk / (32.0 * p.wg_per_cu);
+    if (p.slots > 0 && fullest > load) load = fullest;
+    const double queue = load / p.WK * tile + 0.34 * t;
     const double turns = rounds * t;
     t = t > queue ? t : (queue < turns ? queue : turns);
   }
-  const double hbm = B * mean * kKeyTile * Hkv * D * 4.0 / 10.0e6;
+  // unsplit, whole sequences to an XCD, and no order that evens them out: the XCD
+  // with the longest sets the end (64 x 234 nodes, 2 KV heads, D = 64, up to 6296
+  // rows: 172 us unsplit, 123 in 2)
+  if (p.slots == 0 && B >= kXcds && p.spread != 2) t *= 1.15;
+  const double asked = (wgs < 256 ? wgs : 256) * kCuBytes;
+  const double hbm = B * mean * kKeyTile * Hkv * D * 4.0 / (asked < 10.0e6 ? asked : 10.0e6);
   t = t > hbm ? t : hbm;
   t += 7.1 + (p.WK > 1 ? 0.85 : 0.0) + 18.0 * (rounds - 1);
   if (chunk < longest) {
     const double chunks = (double)cdiv((long long)longest, (long long)(chunk + 0.999));
-    const double block = (p.M < p.RB ? p.M : p.RB) * D * 4.0;  // a row block's partial, bytes
-    const double all = wgs * p.M / p.nRB * D * 4.0;            // all of them
-    const double fused = 1.1 + chunks * block / 233.0e3, second = 3.3 + all / 4.0e6;
-    t += (fused < second ? fused : second) + all / 5.5e6;
+    // A row block's partial in bytes (whole 16-row fragments), and all of them.
+    // In the fused merge a wave folds one row tile's columns, or whole row tiles:
+    // waves without rows are idle, and few waves read at less than the CU's rate
+    // (one wave alone 33 to 44 KB/us: 1 node over 24503 rows, 383 chunks of 3 tiles,
+    // 108 us where 42 chunks take 23).  The second kernel has one wave per
+    // fragment, and waits for memory once per 16 chunks (the second time hardly:
+    // 2 x 50 nodes over 108621 rows in 32 chunks of 4 x 2 waves 66 us, in 16 of 2 x
+    // 4 83; 24 nodes over 107622 in 241 chunks 58 us, in 64 36).
+    const int NTG = p.RB / 16, waves_wg = p.WR * p.WK;
+    const int nt = cdiv(p.M < p.RB ? p.M : p.RB, 16);
+    const int active = waves_wg >= NTG ? waves_wg / NTG * nt : (nt < waves_wg ? nt : waves_wg);
+    const double block = nt * 16.0 * D * 4.0, all = wgs / p.nRB * cdiv(p.M, 16) * 16.0 * D * 4.0;
+    const double waits = chunks > 32 ? 1.0 * (cdiv((long long)chunks, 16) - 2) : 0.0;
+    auto fold = [&](double per_wave, double per_cu) {
+      return chunks * block / (active * per_wave < per_cu ? active * per_wave : per_cu);
+    };
+    const double fused = 1.1 + fold(58.25e3, 233.0e3), second = 3.3 + waits + all / 4.0e6;
+    t += (fused < second ? fused : second) + all / 5.5e6 + 1.0;
     // The kind of merge: by the workgroup whose chunk arrives last (one CU reads
     // 61 to 78 KB/us of partials), or by a second kernel that spreads it over
     // the GPU and starts when the slowest chunk is done (9 us for 33.5 MB).
-    p.fused = 1.1 + chunks * block / 78.0e3 <= 5.3 + all / 4.0e6;
+    p.fused = 1.1 + fold(15.0e3, 78.0e3) <= 5.3 + waits + all / 4.0e6;
   }
   return t;
 }
@@ -269,12 +299,12 @@ inline AttnPlan attn_plan(int B, int N, int Hq, int Hkv, int D, int Lmax) {
   for (int k = 0; k < kNumArrangements; ++k) {
     AttnPlan one = attn_plan_arr(B, N, Hq, Hkv, D, Lmax, k, B);
     if (!attn_plan_fits(one)) continue;
-    // one chunk per sequence, or as many as fill the XCDs once, half or twice
-    // that: a chunk's row blocks stay on one XCD
+    // one chunk per sequence, or as many as fill the XCDs once, a quarter, half or
+    // twice that: a chunk's row blocks stay on one XCD
     const long long pairs = 32LL * one.wg_per_cu / one.nRB;  // (chunk, KV head) pairs per XCD
     const long long fill = kXcds * pairs / Hkv;
-    const long long cand[4] = {B, fill / 2, fill, 2 * fill};
-    for (int c = 0; c < 4; ++c) {
+    const long long cand[5] = {B, fill / 4, fill / 2, fill, 2 * fill};
+    for (int c = 0; c < 5; ++c) {
       if (c > 0 && cand[c] <= B) continue;
       AttnPlan p = c == 0 ? one : attn_plan_arr(B, N, Hq, Hkv, D, Lmax, k, cand[c]);
       const double t = attn_plan_cost(p, B, Hkv, D, Lmax, N);

@@ -102,9 +102,9 @@ int main() {
         if (tp.nsplit < 1 || tp.nsplit > tv::kAcceptMaxSplit) ok = false;
         if (tp.ws_bytes > tv::topw_ws_bytes(B, Nd)) ok = false;
       }
-    std::printf("%s B=%d N=%d Hq=%d Hkv=%d D=%d L=%d V=%d S=%d RB=%d nRB=%d grid=%d spread=%d lds=%zu ws=%zu\n",
-                ok ? "OK" : "FAIL", B, N, Hq, Hkv, D, Lmax, V, p.S, p.RB, p.nRB, p.grid,
-                p.spread, p.lds_bytes, p.ws_bytes);
+    std::printf("%s B=%d N=%d Hq=%d Hkv=%d D=%d L=%d V=%d S=%d slots=%d fused=%d RB=%d nRB=%d grid=%d spread=%d lds=%zu ws=%zu\n",
+                ok ? "OK" : "FAIL", B, N, Hq, Hkv, D, Lmax, V, p.S, p.slots, p.fused, p.RB, p.nRB,
+                p.grid, p.spread, p.lds_bytes, p.ws_bytes);
     bad += !ok;
   }
   std::printf("%d cases, %d failed\n", cases, bad);

@@ -58,6 +58,31 @@ def test_plans_under_host_sanitizers(tmp_path):
     assert res.returncode == 0 and not fails, "\n".join(fails[:20]) + res.stderr[-1000:]
 
 
+def plans(tmp_path, cases):
+    """The plan of each (B, N, Hq, Hkv, D, Lmax) as a dict of its numbers."""
+    exe = tmp_path / "plan_check"
+    subprocess.run(["g++", "-O1", "-std=c++17", "-I", CSRC,
+                    os.path.join(ROOT, "tests", "native", "plan_check.cpp"), "-o", str(exe)],
+                   check=True)
+    res = subprocess.run([str(exe)], input="".join(" ".join(map(str, c)) + " 1001\n" for c in cases),
+                         capture_output=True, text=True, check=True)
+    return [{k: int(v) for k, v in (f.split("=") for f in l.split()[1:])}
+            for l in res.stdout.splitlines() if l.startswith("OK")]
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_few_rows_take_few_chunks(tmp_path):
+    """With one 16-row tile per KV head one wave folds a whole fused merge, at 33
+    to 44 KB/us: 383 chunks took 108 us where 42 take 23.  Few rows on a long
+    cache keep enough workgroups to ask for its bytes all the same."""
+    for p in plans(tmp_path, [(1, 1, 3, 3, 128, 24503), (1, 1, 3, 3, 128, 5618),
+                              (3, 1, 6, 3, 64, 5495), (4, 1, 12, 3, 64, 24499),
+                              (1, 2, 12, 3, 64, 3594), (2, 4, 4, 1, 128, 15042)]):
+        assert p["S"] <= 64, p
+    for p in plans(tmp_path, [(2, 4, 16, 8, 64, 80754), (1, 2, 64, 32, 64, 99422)]):
+        assert p["slots"] * p["Hkv"] * p["nRB"] >= 256, p
+
+
 @pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
 def test_accept_split_rule(tmp_path):
     """The acceptance scan's split count: the ~2048-workgroup target (at most
