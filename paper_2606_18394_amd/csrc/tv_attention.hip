@@ -227,37 +227,73 @@ __device__ __forceinline__ EvenItem even_one(const AttnArgs& a, int item) {
   return EvenItem{chunk, 0, item * chunk < t ? item : -1, 0, kvl};
 }
 
-// Several, one per lane.  The tiles are those of the last row block: a chunk's
-// row blocks read the same keys.  With item < 0 it is sequence b that is looked
-// up (its s is then of no use).
+// Several, P consecutive ones per lane (all slots are computed, those past the
+// batch hold no tiles: a branch over each costs more than it skips).  The tiles
+// are those of the last row block: a chunk's row blocks read the same keys.  With
+// item < 0 it is sequence b that is looked up (its s is then of no use).
+template <int P>
 __device__ __forceinline__ EvenItem even_lanes(const AttnArgs& a, int item, int b) {
-  const int lane = threadIdx.x & 63;
-  const int kvl = context_rows(a, min(lane, a.B - 1));
-  const int t = lane < a.B ? segment(a, kvl, a.N - 1).T : 0;
-  const float total = (float)wave_sum(t);
-  const int longest = (int)wave_max_u32((unsigned)t);
+  const int b0 = P * (threadIdx.x & 63);
+  int kvl[P], t[P], n[P], sum = 0, most = 0;
+#pragma unroll
+  for (int k = 0; k < P; ++k) kvl[k] = context_rows(a, min(b0 + k, a.B - 1));
+#pragma unroll
+  for (int k = 0; k < P; ++k) {
+    t[k] = b0 + k < a.B ? segment(a, kvl[k], a.N - 1).T : 0;
+    sum += t[k];
+    most = max(most, t[k]);
+  }
+  const float total = (float)wave_sum(sum);
+  const int longest = (int)wave_max_u32((unsigned)most);
   // Chunks of less than total / slots tiles are too many, those of total /
   // (slots - B) few enough (the sum of ceil(t / c) is below total / c + B); the
   // margins cover the rounding.
   int lo = max(a.min_chunk - 1, (int)(total * a.rslots * 0.999999f) - 1);
   int hi = max(min(longest, (int)(total * a.rslack * 1.000001f) + 1), lo + 1);
-  auto chunks = [&](int c) { return ceil_div(t, c, __builtin_amdgcn_rcpf((float)c)); };
+  auto chunks = [&](int c) {
+    const float rc = __builtin_amdgcn_rcpf((float)c);
+    int s = 0;
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+      n[k] = ceil_div(t[k], c, rc);
+      s += n[k];
+    }
+    return s;
+  };
   while (hi - lo > 1) {
     const int mid = lo + ((hi - lo) >> 1);
     if (wave_sum(chunks(mid)) <= a.slots) hi = mid;
     else lo = mid;
   }
-  const int n = chunks(hi), upto = wave_scan(n);
-  // the last sequence that starts at or before the item
-  if (item >= 0) b = __popcll(__ballot(lane < a.B && upto - n <= item)) - 1;
-  const int first = __builtin_amdgcn_readlane(upto - n, b);
-  return EvenItem{hi, b, item < __builtin_amdgcn_readlane(upto, 63) ? item - first : -1, first,
-                  __builtin_amdgcn_readlane(kvl, b)};
+  const int upto = wave_scan(chunks(hi));
+  int first = upto;
+#pragma unroll
+  for (int k = 0; k < P; ++k) first -= n[k];
+  // the last sequence that starts at or before the item: its lane, then its
+  // place there (every sequence has a chunk, so places past the batch start with
+  // the lane after them)
+  const int owner = item < 0 ? b / P : __popcll(__ballot(b0 < a.B && first <= item)) - 1;
+  int place = 0, kv = kvl[0], end = first + n[0];
+#pragma unroll
+  for (int k = 1; k < P; ++k) {
+    const bool next = item < 0 ? b % P >= k : end <= item && b0 + k < a.B;
+    place = next ? k : place;
+    kv = next ? kvl[k] : kv;
+    first = next ? end : first;
+    end += n[k];
+  }
+  first = __builtin_amdgcn_readlane(first, owner);
+  return EvenItem{hi, P * owner + __builtin_amdgcn_readlane(place, owner),
+                  item < __builtin_amdgcn_readlane(upto, 63) ? item - first : -1, first,
+                  __builtin_amdgcn_readlane(kv, owner)};
 }
 
 // Work item `item` of the batch, or (item < 0) what concerns sequence b.
 __device__ __forceinline__ EvenItem even_split(const AttnArgs& a, int item, int b) {
-  return a.B == 1 ? even_one(a, item) : even_lanes(a, item, b);
+  static_assert(kEvenSequences == 16 * 64, "sequences per lane");
+  if (a.B == 1) return even_one(a, item);
+  if (a.B <= 64) return even_lanes<1>(a, item, b);
+  return a.B <= 256 ? even_lanes<4>(a, item, b) : even_lanes<16>(a, item, b);
 }
 
 // Four output values, or four NaN when the sequence's tree is invalid (the

@@ -30,7 +30,7 @@ constexpr int kRowsPerWave = 32;
 constexpr int kSyncGroups = 4096;
 constexpr size_t kSyncBytes = (size_t)kSyncGroups * 8;
 constexpr int kWavesPerCU = 8;
-constexpr int kEvenSequences = 64;  // batches the even split takes (one per lane)
+constexpr int kEvenSequences = 1024;  // batches the even split takes (up to 16 per lane)
 constexpr size_t kMaxLds = 160 * 1024;
 
 struct Arrangement {
@@ -287,6 +287,8 @@ inline double attn_plan_cost(AttnPlan& p, int B, int Hkv, int D, int Lmax, int N
     // The kind of merge: by the workgroup whose chunk arrives last (one CU reads
     // 61 to 78 KB/us of partials), or by a second kernel that spreads it over
     // the GPU and starts when the slowest chunk is done (9 us for 33.5 MB).
+    // more than 64 sequences: several per lane in the search for a work item
+    if (B > 64) t += B > 256 ? 5.0 : 2.0;
     p.fused = 1.1 + fold(15.0e3, 78.0e3) <= 5.3 + waits + all / 4.0e6;
   }
   return t;
@@ -305,7 +307,13 @@ inline AttnPlan attn_plan(int B, int N, int Hq, int Hkv, int D, int Lmax) {
     const long long fill = kXcds * pairs / Hkv;
     const long long cand[5] = {B, fill / 4, fill / 2, fill, 2 * fill};
     for (int c = 0; c < 5; ++c) {
-      if (c > 0 && cand[c] <= B) continue;
+      // a few chunks more than sequences split next to none of them
+      if (c > 0 && 2 * cand[c] < 3LL * B) continue;
+      // (of more than 64 sequences only those whose row blocks leave CUs empty, half
+      // of them where the longest go first (spread): 100 nodes, 32 heads on 8, D =
+      // 64, up to 7273 rows 153 us unsplit, 201 in 2)
+      const long long places = one.spread == 2 ? 128LL : 256LL;
+      if (c > 0 && B > 64 && (long long)B * Hkv * one.nRB >= places * one.wg_per_cu) continue;
       AttnPlan p = c == 0 ? one : attn_plan_arr(B, N, Hq, Hkv, D, Lmax, k, cand[c]);
       const double t = attn_plan_cost(p, B, Hkv, D, Lmax, N);
       if (!have || t < best_cost) {

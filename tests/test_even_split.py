@@ -40,10 +40,12 @@ LENGTHS = {
 @pytest.mark.gpu
 @pytest.mark.parametrize("kind", sorted(LENGTHS))
 @pytest.mark.parametrize("shape", [
-    # (B, N, Hq, Hkv, D, capacity): one sequence; few; a lane for each; past the lanes
+    # (B, N, Hq, Hkv, D, capacity): one sequence; few; a lane for each; several
+    # to a lane (4, above 256 16), the last lanes with fewer or none
     (1, 33, 8, 2, 128, 3000), (1, 200, 8, 1, 64, 4000), (2, 40, 4, 2, 128, 2500),
     (5, 70, 12, 3, 64, 1500), (16, 9, 8, 4, 128, 1200), (64, 3, 4, 2, 64, 700),
-    (65, 3, 4, 2, 64, 700),
+    (65, 3, 4, 2, 64, 700), (130, 2, 4, 1, 128, 900), (255, 1, 2, 1, 64, 500), (257, 1, 1, 1, 64, 700),
+    (600, 1, 1, 1, 64, 500),
 ])
 def test_lengths(shape, kind):
     """Max-abs error at most 1.5e-2: rounding the softmax weights and the

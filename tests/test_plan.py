@@ -84,6 +84,20 @@ def test_few_rows_take_few_chunks(tmp_path):
 
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_batches_beyond_a_wave_still_split(tmp_path):
+    """Long sequences of few KV heads are split on both sides of 64 sequences
+    (one to a lane below, several above), up to 1024; those whose row blocks fill
+    the GPU are not above 64."""
+    split = [(B, N, Hq, Hkv, 128, L) for B in (63, 64, 65, 80, 200)
+             for N, Hq, Hkv, L in ((33, 4, 1, 16384), (9, 4, 1, 3776), (3, 8, 1, 8192))
+             if B * Hkv < 256]
+    for p in plans(tmp_path, split):
+        assert p["slots"] >= 2 * p["B"] and p["S"] > 1, p
+    for p in plans(tmp_path, [(100, 1, 32, 8, 64, 7273), (1025, 1, 1, 1, 64, 4000)]):
+        assert p["slots"] == 0 and p["S"] == 1, p
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
 def test_accept_split_rule(tmp_path):
     """The acceptance scan's split count: the ~2048-workgroup target (at most
     16 splits, at least one full round of loads each), then down to half of
