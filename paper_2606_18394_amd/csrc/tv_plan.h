@@ -329,17 +329,21 @@ inline AttnPlan attn_plan(int B, int N, int Hq, int Hkv, int D, int Lmax) {
 // Training-mask calls with several blocks to a workgroup (tv_attention.hip,
 // attn_packed): blocks of at most 64 rows (of more, a workgroup of 128 rows
 // holds one), few enough for the sort, and enough of them that one block per
-// workgroup would take more than two rounds of the chip's 512 places; below that
-// the packs are too few and their long tile chains cost more than they save.
-// Measured (8 KV heads, D = 128, anchors spread over 2048 positions; packed
-// against one block each): M = 64 rows: 63.6 against 46.6 us at 512 blocks x
-// heads, 45.1 against 47.2 at 1024 (1000 positions); M = 32: 64 against 33 at 512, 66 against 67 at
-// 1024, 72 against 81 at 1536; M = 16: 68 against 66 at 1024, 69 against 96 at
-// 2048; M = 8: 76 against 65 at 1024, 76 against 92 at 2048, 80 against 200 at
-// 4096.  The order of the blocks lies behind the sync words of the workspace.
+// workgroup would take well more than two rounds of the chip's 512 places; below
+// that the packs are too few and their long tile chains cost more than they save.
+// With n = examples x blocks x KV heads that is from 1280 on, for blocks of less
+// than 16 rows (16 to a pack: the fewest packs) from 1800, and half a group more
+// for every block of an example past 256, since the sort compares each with all.
+// Measured on 260 shapes, one block each against packed: M = 16 rows, n = 1584,
+// 186 positions 28.9 against 25.1 us, 2016, 1344 positions 95.5 against 54.1; M =
+// 32, 1408, 245 positions 30.4 against 24.6; M = 64, 2048, 256 positions 40.4
+// against 27.4; M = 8, 1677, 424 positions 33.5 against 41.8 (not packed), 2208,
+// 247 positions 50.7 against 34.9; 1584 blocks of 16 rows of one head 25.5 against
+// 33.6 (not packed).  The order of the blocks lies behind the sync words of the
+// workspace.
 constexpr int kPackRows = 128;
 constexpr int kPackMaxBlocks = 2048;  // blocks per example the sort takes
-constexpr int kPackMinGroups = 1280;  // examples x blocks x KV heads
+constexpr int kPackMinGroups = 1280, kPackMinSmall = 1800;  // n, for M >= 16 and below
 constexpr int kPackRank = 64;         // blocks a workgroup of the sort ranks
 struct PackPlan {
   int nb, packs;  // blocks per workgroup (0: not packed), workgroups per (example, KV head)
@@ -351,7 +355,8 @@ inline PackPlan pack_plan(int B, int A, int S, int Hq, int Hkv) {
   if (2 * M > kPackRows || A > kPackMaxBlocks) return p;
   const int nb = (int)(kPackRows / M) < 16 ? (int)(kPackRows / M) : 16;
   const int packs = cdiv(A, nb);
-  if (A < nb || (long long)B * A * Hkv < kPackMinGroups) return p;
+  const long long least = (M >= 16 ? kPackMinGroups : kPackMinSmall) + (A > 256 ? (A - 256) / 2 : 0);
+  if (A < nb || (long long)B * A * Hkv < least) return p;
   p.nb = nb;
   p.packs = packs;
   p.ws_bytes = kSyncBytes + (size_t)B * A * 4;

@@ -98,6 +98,28 @@ def test_batches_beyond_a_wave_still_split(tmp_path):
 
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_pack_rule(tmp_path):
+    """Where the training mask packs several blocks into a workgroup, on both
+    sides of the line: by blocks x KV heads, later for blocks of few rows and for
+    many blocks of one example."""
+    exe = tmp_path / "pack_check"
+    subprocess.run(["g++", "-O1", "-std=c++17", "-I", CSRC,
+                    os.path.join(ROOT, "tests", "native", "pack_check.cpp"), "-o", str(exe)],
+                   check=True)
+    cases = [((1, 160, 16, 32, 8), 2), ((1, 159, 16, 32, 8), 0), ((1, 80, 16, 16, 16), 8),
+             ((3, 559, 1, 8, 1), 0), ((1, 224, 2, 32, 8), 0), ((1, 226, 2, 32, 8), 16),
+             ((1, 1584, 16, 1, 1), 0), ((1, 1863, 2, 2, 2), 16), ((1, 512, 16, 32, 8), 2),
+             ((1, 2049, 16, 32, 8), 0), ((1, 512, 17, 32, 8), 0)]
+    res = subprocess.run([str(exe)], input="".join(" ".join(map(str, c)) + "\n" for c, _ in cases),
+                         capture_output=True, text=True, check=True)
+    for (c, nb), line in zip(cases, res.stdout.splitlines()):
+        got, packs, ws = map(int, line.split())
+        assert got == nb, (c, got)
+        if nb:
+            assert packs == -(-c[1] // nb) and ws == 32768 + 4 * c[0] * c[1], (c, line)
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
 def test_accept_split_rule(tmp_path):
     """The acceptance scan's split count: the ~2048-workgroup target (at most
     16 splits, at least one full round of loads each), then down to half of
