@@ -62,6 +62,21 @@ static const tv::AttnPlan& attn_plan_of(int B, int N, int Hq, int Hkv, int D, in
   return last.plan;
 }
 
+// The plan that a call's workspace allows: the shape's, or the fixed split's
+// where that is enough; ok says whether either is.
+static tv::AttnPlan attn_plan_within(int B, int N, int Hq, int Hkv, int D, int Lmax,
+                                     const void* workspace, size_t bytes, bool& ok) {
+  auto fits = [&](const tv::AttnPlan& p) {
+    return p.ws_bytes == 0 || (workspace && bytes >= p.ws_bytes);
+  };
+  const tv::AttnPlan& p = attn_plan_of(B, N, Hq, Hkv, D, Lmax);
+  ok = fits(p);
+  if (ok) return p;
+  const tv::AttnPlan q = tv::attn_plan_fixed(B, N, Hq, Hkv, D, Lmax);
+  ok = fits(q);
+  return q;
+}
+
 static bool misaligned(const void* p) { return ((uintptr_t)p & 15u) != 0; }
 
 static int check_attention_sizes(int B, int N, int Hq, int Hkv, int D, int Lmax) {
@@ -153,8 +168,9 @@ int tv_tree_verify_attention(const void* q, const void* k_cache, const void* v_c
   if (misaligned(q) || misaligned(out) ||
       (Lmax > 0 && (misaligned(k_cache) || misaligned(v_cache))))
     return TV_ERR_ALIGN;
-  const tv::AttnPlan& p = attn_plan_of(B, N, Hq, Hkv, D, Lmax);
-  if (p.ws_bytes > 0 && (!workspace || workspace_bytes < p.ws_bytes)) return TV_ERR_WORKSPACE;
+  bool ok;
+  const tv::AttnPlan p = attn_plan_within(B, N, Hq, Hkv, D, Lmax, workspace, workspace_bytes, ok);
+  if (!ok) return TV_ERR_WORKSPACE;
   if (misaligned(workspace)) return TV_ERR_ALIGN;
   if (!(scale > 0.f)) scale = 1.0f / sqrtf((float)D);
   hipError_t e = tv::launch_attention(q, k_cache, v_cache, k_tree, v_tree, parent, kv_len, out,
@@ -186,16 +202,17 @@ int tv_block_causal_attention(const void* q, const void* k_ctx, const void* v_ct
     return TV_ERR_ALIGN;
   if (!(scale > 0.f)) scale = 1.0f / sqrtf((float)D);
   const tv::PackPlan pk = tv::pack_plan(B, A, S, Hq, Hkv);
-  // (a smaller workspace, or none, is enough for one block per workgroup
-  // where that plan does not split)
+  // (a smaller workspace, or none, is enough for one block per workgroup where
+  // a plan within it does not split)
   if (pk.nb > 0 && workspace && workspace_bytes >= pk.ws_bytes) {
     if (misaligned(workspace)) return TV_ERR_ALIGN;
     const hipError_t e = tv::launch_packed(q, k_ctx, v_ctx, k_blk, v_blk, anchors, out, B, A, S, Hq,
                                            Hkv, D, L, scale, workspace, pk, stream);
     return e == hipSuccess ? TV_OK : TV_ERR_LAUNCH;
   }
-  const tv::AttnPlan& p = attn_plan_of(B * A, S, Hq, Hkv, D, L);
-  if (p.ws_bytes > 0 && (!workspace || workspace_bytes < p.ws_bytes)) return TV_ERR_WORKSPACE;
+  bool ok;
+  const tv::AttnPlan p = attn_plan_within(B * A, S, Hq, Hkv, D, L, workspace, workspace_bytes, ok);
+  if (!ok) return TV_ERR_WORKSPACE;
   if (misaligned(workspace)) return TV_ERR_ALIGN;
   hipError_t e = tv::launch_attention(q, k_ctx, v_ctx, k_blk, v_blk, nullptr, anchors, out,
                                       B * A, S, Hq, Hkv, D, L, scale, workspace, p, stream,
@@ -222,8 +239,9 @@ int tv_tree_verify_attention_paged(const void* q, const void* k_pool, const void
   if (misaligned(q) || misaligned(out) ||
       (Lmax > 0 && (misaligned(k_pool) || misaligned(v_pool))))
     return TV_ERR_ALIGN;
-  const tv::AttnPlan& p = attn_plan_of(B, N, Hq, Hkv, D, Lmax);
-  if (p.ws_bytes > 0 && (!workspace || workspace_bytes < p.ws_bytes)) return TV_ERR_WORKSPACE;
+  bool ok;
+  const tv::AttnPlan p = attn_plan_within(B, N, Hq, Hkv, D, Lmax, workspace, workspace_bytes, ok);
+  if (!ok) return TV_ERR_WORKSPACE;
   if (misaligned(workspace)) return TV_ERR_ALIGN;
   if (!(scale > 0.f)) scale = 1.0f / sqrtf((float)D);
   hipError_t e = tv::launch_attention(q, k_pool, v_pool, k_tree, v_tree, parent, kv_len, out, B,

@@ -31,6 +31,7 @@ constexpr int kSyncGroups = 4096;
 constexpr size_t kSyncBytes = (size_t)kSyncGroups * 8;
 constexpr int kWavesPerCU = 8;
 constexpr int kEvenSequences = 1024;  // batches the even split takes (up to 16 per lane)
+constexpr int kEvenTiles = 1 << 20;   // key tiles a sequence of it has fewer than
 constexpr size_t kMaxLds = 160 * 1024;
 
 struct Arrangement {
@@ -74,8 +75,10 @@ inline size_t attn_lds_bytes(int D, int WR, int WK, int NS, int G, int N, bool q
 }
 
 // The plan for one arrangement and `want` chunks per (KV head, row block) over
-// all sequences (at least B; B: no split).
-inline AttnPlan attn_plan_arr(int B, int N, int Hq, int Hkv, int D, int Lmax, int arr, long long want) {
+// all sequences (at least B; B: no split), of one size for the whole batch or
+// (even = false) want / B of each sequence's capacity.
+inline AttnPlan attn_plan_arr(int B, int N, int Hq, int Hkv, int D, int Lmax, int arr, long long want,
+                              bool even = true) {
   const Arrangement& ar = kArrangements[arr];
   AttnPlan p{};
   p.arr = arr;
@@ -95,12 +98,12 @@ inline AttnPlan attn_plan_arr(int B, int N, int Hq, int Hkv, int D, int Lmax, in
   const long long max_s = tiles / min_chunk > 1 ? tiles / min_chunk : 1;
   long long S = (want + B - 1) / B;
   if (S > max_s) S = max_s;
-  if (S < 1 || base > kSyncGroups || (B > kEvenSequences && S > 1) || tiles >= (1 << 20)) S = 1;
+  if (S < 1 || base > kSyncGroups || (even && (B > kEvenSequences || tiles >= kEvenTiles))) S = 1;
   p.chunk = cdiv(tiles, S);
   p.S = cdiv(tiles, p.chunk);
   p.nwork = (int)(base * p.S);
   p.grid = cdiv(p.nwork, kXcds) * kXcds;
-  if (p.S > 1) {
+  if (p.S > 1 && even) {
     p.slots = (int)(want < (long long)B * p.S ? want : (long long)B * p.S);
     p.min_chunk = min_chunk;
     p.even_grid = kXcds * p.nRB * cdiv((long long)p.slots * Hkv, kXcds);
@@ -294,7 +297,55 @@ inline double attn_plan_cost(AttnPlan& p, int B, int Hkv, int D, int Lmax, int N
   return t;
 }
 
+// The fixed split: S chunks of every sequence's capacity, in the arrangement that
+// a rough price picks.  Calls that bring less workspace than the plan below asks
+// for run on it where it asks for less: they were accepted before there was an
+// even split, whose plans cut shapes that this one leaves whole (16 x 33 nodes, 32
+// heads on 8, 4160 rows: 38 MB against none).
+//
+// Price: matrix work on padded rows, K/V traffic from L2 (each row block re-reads
+// the keys), HBM, the split partials written and read back, a penalty when the two
+// waves of a SIMD belong to one workgroup (its per-tile barriers keep them in
+// phase, so their matrix and vector work overlap poorly), and a fixed cost per
+// round of workgroups.
+inline AttnPlan attn_plan_fixed(int B, int N, int Hq, int Hkv, int D, int Lmax) {
+  AttnPlan best{};
+  double best_cost = 0;
+  bool have = false;
+  for (int k = 0; k < kNumArrangements; ++k) {
+    AttnPlan p = attn_plan_arr(B, N, Hq, Hkv, D, Lmax, k, B, false);
+    const long long base = (long long)B * Hkv * p.nRB, target = 256LL * p.wg_per_cu;
+    const int tiles = cdiv(Lmax, kKeyTile) + cdiv(N, kKeyTile);
+    const long long max_s = tiles / (2 * p.WK) > 1 ? tiles / (2 * p.WK) : 1;
+    long long S = (target + base - 1) / base;
+    if (S > max_s) S = max_s;
+    if (B > 1 && base < target && S < 4 && max_s >= 4) S = 4;  // ragged batches
+    if (S > 1) p = attn_plan_arr(B, N, Hq, Hkv, D, Lmax, k, S * B, false);
+    if (!attn_plan_fits(p)) continue;
+    // the last chunk of a row block merges all of them when that takes at most two
+    // batches of loads per lane, else a second kernel does
+    p.fused = p.S > 1 && (size_t)p.S * p.RB * D * 4 <= (size_t)1024 * p.threads;
+    const double keys = (double)Lmax + N;
+    double mfma = (double)B * Hkv * p.nRB * p.RB * keys * 4.0 * D / 2.0e15;
+    if (p.wg_per_cu == 1 && p.WR > 1) mfma *= 1.3;
+    const double kv = (double)B * Hkv * keys * D * 4.0;
+    const double l2 = kv * p.nRB / 20.0e12, hbm = kv / 6.0e12;
+    double t = mfma > l2 ? mfma : l2;
+    t = t > hbm ? t : hbm;
+    t += (double)p.ws_bytes * 2.0 / 5.0e12 + cdiv(p.nwork, target) * 4.0e-6;
+    if (!have || t < best_cost) {
+      best = p;
+      best_cost = t;
+      have = true;
+    }
+  }
+  return best;
+}
+
 inline AttnPlan attn_plan(int B, int N, int Hq, int Hkv, int D, int Lmax) {
+  // (the even split's quotients hold below 2^20 tiles)
+  if (cdiv(Lmax, kKeyTile) + cdiv(N, kKeyTile) >= kEvenTiles)
+    return attn_plan_fixed(B, N, Hq, Hkv, D, Lmax);
   AttnPlan best{};
   double best_cost = 0;
   bool have = false;

@@ -124,3 +124,55 @@ def test_partials_hold_the_rows_only(shape):
     written = int((ws[32768:] != 0xA5).sum())
     print(f"{written} of {need - 32768} bytes", flush=True)
     assert 0 < written <= (need - 32768) // 2
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [
+    # (B, N, Hq, Hkv, D, rows): the fixed split's plan needs no workspace (one, several
+    # and more than 64 sequences, longest first), then less than the even split's (a
+    # lane of chunks per XCD of 1, 2, 4 and 8, and none)
+    (1, 39, 3, 3, 128, 353), (2, 2, 16, 4, 128, 437), (35, 8, 16, 8, 64, 790),
+    (174, 6, 3, 3, 128, 168), (2, 6, 16, 8, 128, 459), (2, 14, 4, 4, 128, 458),
+    (8, 3, 8, 2, 64, 2097), (2, 3, 8, 1, 64, 4165), (1, 18, 3, 3, 64, 5465), (3, 9, 2, 1, 64, 2655),
+])
+def test_less_workspace(shape):
+    """A call with less workspace than the query says is computed as long as the
+    fixed split's plan fits in it, and refused one byte below."""
+    import torch
+    from helpers import dev_bf16, dev_i32, oracle_attention
+    from paper_2606_18394_amd import tree_verify_attention
+    from paper_2606_18394_amd.binding import load_library
+    B, N, Hq, Hkv, D, L = shape
+    rng = np.random.default_rng(B * 100 + L)
+    trees = np.stack([synth.random_tree(rng, N, depth=min(N - 1, 9), branching=4) for _ in range(B)])
+    inp = synth.make_inputs(rng, B=B, N=N, Hq=Hq, Hkv=Hkv, D=D, Lmax=L, V=8, trees=trees,
+                            kv_len=np.array([L - (i * 61) % (L + 1) for i in range(B)]),
+                            with_logits=False)
+    print(shape, flush=True)
+    ref = oracle_attention(inp)
+    q, kc, vc, kt, vt = (dev_bf16(inp[k]) for k in ("q", "k_cache", "v_cache", "k_tree", "v_tree"))
+    par, kvl = dev_i32(inp["parent"]), dev_i32(inp["kv_len"])
+    need = load_library().tv_tree_verify_attention_workspace(B, N, Hq, Hkv, D, L)
+    full = torch.zeros(need, dtype=torch.uint8, device="cuda")
+
+    def call(size):
+        out = torch.zeros_like(q)
+        try:
+            tree_verify_attention(q, kc, vc, kt, vt, par, out, kv_len=kvl, workspace_tensor=full[:size])
+        except RuntimeError as e:
+            assert "WORKSPACE" in str(e)
+            return None
+        torch.cuda.synchronize()
+        return out.float().cpu().numpy()
+    lo, hi = -1, need  # the smallest size that is accepted
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        if call(mid) is None:
+            lo = mid
+        else:
+            hi = mid
+    print(f"{hi} of {need} bytes", flush=True)
+    assert hi < need - 4096
+    for size in (hi, hi, need):
+        assert np.abs(call(size) - ref).max() <= 1.5e-2
+        assert not full[:32768].any(), "sync words left non-zero"
