@@ -32,7 +32,7 @@ hipError_t launch_accept(const void* logits, int f32, const int32_t* draft, cons
                          int B, int N, int V, int Dmax, int32_t* accept_len, int32_t* path,
                          int32_t* tgt_out, void* ws, hipStream_t st);
 hipError_t launch_topw(const void* logits, int f32, int B, int Nd, int V, int W, int32_t* tok,
-                       float* logp, void* ws, hipStream_t st);
+                       float* logp, void* ws, size_t ws_bytes, hipStream_t st);
 hipError_t launch_sample(const void* logits, int f32, const int32_t* draft,
                          const int32_t* parent, const float* u, unsigned long long seed,
                          float temperature, int B, int N, int V, int Dmax, int32_t* accept_len,
@@ -404,7 +404,7 @@ int tv_tree_accept_sampled(const void* logits, int logits_dtype, const int32_t* 
 
 size_t tv_draft_topw_workspace(int B, int Nd, int V) {
   if (check_draft_sizes(B, Nd, 1) != TV_OK || V < 1) return 0;
-  return tv::topw_ws_bytes(B, Nd);
+  return tv::topw_ws_bytes(B, Nd, V);
 }
 
 int tv_draft_topw(const void* logits, int logits_dtype, int B, int Nd, int V, int W,
@@ -415,10 +415,10 @@ int tv_draft_topw(const void* logits, int logits_dtype, int B, int Nd, int V, in
   if (V < 1 || W > V) return TV_ERR_SHAPE;
   if (logits_dtype != TV_BF16 && logits_dtype != TV_F32) return TV_ERR_DTYPE;
   if (!logits || !tok || !logp) return TV_ERR_NULL;
-  if (!workspace || workspace_bytes < tv::topw_ws_bytes(B, Nd)) return TV_ERR_WORKSPACE;
+  if (!workspace || workspace_bytes < tv::topw_min_bytes(B, Nd)) return TV_ERR_WORKSPACE;
   if (misaligned(workspace)) return TV_ERR_ALIGN;
   hipError_t e = tv::launch_topw(logits, logits_dtype == TV_F32, B, Nd, V, W, tok, logp,
-                                 workspace, stream);
+                                 workspace, workspace_bytes, stream);
   return e == hipSuccess ? TV_OK : TV_ERR_LAUNCH;
 }
 

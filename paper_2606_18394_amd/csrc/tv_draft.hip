@@ -240,7 +240,8 @@ __global__ __launch_bounds__(kScanThreads) void topw_scan(TopwArgs a) {
   const char* rowp = (const char*)a.logits + (size_t)row * a.V * (F32 ? 4 : 2);
   const RowSpan<F32> rs(rowp, a.V);
   // the slice: n chunks from `slice` on, whose first element is row element i0;
-  // offsets inside it fit 32 bits (at least 16 splits of such a row)
+  // offsets inside it fit 32 bits (with fewer than 16 splits there are at least
+  // 128 rows, and a slice is at most a 2048th of the logits)
   const int c0 = (int)min((long long)split * a.cps, (long long)rs.chunks);
   const int n = (int)min(a.cps, (long long)(rs.chunks - c0));
   // (without chunks the loads go to the workspace and count for nothing)
@@ -495,9 +496,10 @@ static void launch_topw_scan(int K, dim3 g, hipStream_t st, const TopwArgs& a) {
 }
 
 hipError_t launch_topw(const void* logits, int f32, int B, int Nd, int V, int W, int32_t* tok,
-                       float* logp, void* ws, hipStream_t st) {
+                       float* logp, void* ws, size_t ws_bytes, hipStream_t st) {
   const int esize = f32 ? 4 : 2;
-  const TopwPlan p = topw_plan(B, Nd, V, 16 / esize);
+  const TopwPlan p = topw_plan(B, Nd, V, 16 / esize,
+                               (long long)(ws_bytes / ((size_t)B * Nd * kTopwPartBytes)));
   TopwArgs a;
   a.logits = logits;
   a.tok = tok;

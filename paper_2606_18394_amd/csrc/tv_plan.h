@@ -506,7 +506,8 @@ inline size_t accept_ws_bytes(int B, int N) {
 // each row.  A slice is one round of loads wherever 16 splits allow it (the
 // scan of more rounds keeps lists and runs several times longer), and where
 // that leaves the GPU short of workgroups, up to 16 splits of fewer loads per
-// thread.
+// thread.  Calls may bring less workspace than that takes, down to the acceptance
+// scan's split cap (topw_min_bytes); they get as many splits as it holds.
 constexpr int kTopwMax = 16;             // largest branching width W
 constexpr int kMaxDraftDepth = 64;       // == TV_MAX_DRAFT_DEPTH
 constexpr size_t kTopwPartBytes = 8 + 8 * kTopwMax;
@@ -519,7 +520,8 @@ struct TopwPlan {
   size_t ws_bytes;
 };
 
-inline TopwPlan topw_plan(int B, int Nd, int V, int vec_elems) {
+inline TopwPlan topw_plan(int B, int Nd, int V, int vec_elems,
+                          long long most_splits = kAcceptMaxSplit) {
   TopwPlan p{};
   const long long rows = (long long)B * Nd;
   const long long chunks = (V + vec_elems - 1) / vec_elems;
@@ -527,7 +529,8 @@ inline TopwPlan topw_plan(int B, int Nd, int V, int vec_elems) {
   long long ns = (chunks + per_round - 1) / per_round;
   const long long fill = (512 + rows - 1) / rows, whole = chunks / kScanThreads;  // >= 1 load each
   if (ns < fill) ns = fill < whole ? fill : whole;
-  if (ns > kAcceptMaxSplit) ns = kAcceptMaxSplit;
+  if (most_splits > kAcceptMaxSplit) most_splits = kAcceptMaxSplit;
+  if (ns > most_splits) ns = most_splits;
   if (ns < 1) ns = 1;
   p.chunks_per_split = (chunks + ns - 1) / ns;
   p.nsplit = (int)((chunks + p.chunks_per_split - 1) / p.chunks_per_split);
@@ -536,8 +539,16 @@ inline TopwPlan topw_plan(int B, int Nd, int V, int vec_elems) {
   return p;
 }
 
-inline size_t topw_ws_bytes(int B, int Nd) {
-  return (size_t)B * Nd * kAcceptMaxSplit * kTopwPartBytes;
+// The least workspace a call is accepted with, and what the plan of either dtype
+// asks for.
+inline size_t topw_min_bytes(int B, int Nd) {
+  const long long rows = (long long)B * Nd;
+  return (size_t)(rows * accept_split_cap(rows)) * kTopwPartBytes;
+}
+inline size_t topw_ws_bytes(int B, int Nd, int V) {
+  const size_t f32 = topw_plan(B, Nd, V, 4).ws_bytes, bf16 = topw_plan(B, Nd, V, 8).ws_bytes;
+  const size_t most = f32 > bf16 ? f32 : bf16, least = topw_min_bytes(B, Nd);
+  return most > least ? most : least;
 }
 
 // Non-greedy acceptance: an lse scan over the B*N target rows (splits as

@@ -90,3 +90,25 @@ def test_topw_rounds(shape):
     rt, rlp = oracle.draft_topw(ref, 8)
     np.testing.assert_array_equal(t, rt)
     assert np.abs(lp - rlp).max() <= 1e-5
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_topw_less_workspace(dtype):
+    """2048 rows: the query asks for the splits of the plan; half of that, one
+    split per row, is enough for the same result, and less is refused."""
+    from paper_2606_18394_amd import draft_topw
+    from paper_2606_18394_amd.binding import load_library
+    B, Nd, V, W = 32, 64, 16640, 4
+    print(dtype, flush=True)
+    x = torch.randn(B, Nd, V, generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+    x = x if dtype == "f32" else x.to(torch.bfloat16)
+    v, i = torch.sort(x.double(), dim=-1, descending=True, stable=True)
+    ref = v[..., :W] - torch.logsumexp(v, -1, keepdim=True)
+    need, least = load_library().tv_draft_topw_workspace(B, Nd, V), B * Nd * 136
+    assert need >= 2 * least
+    for size in (least, 2 * least - 1, need):
+        tok, lp = draft_topw(x, W, workspace_tensor=torch.empty(size, dtype=torch.uint8, device="cuda"))
+        assert torch.equal(tok.long(), i[..., :W])
+        assert (lp.double() - ref).abs().max().item() <= 1e-5
+    with pytest.raises(RuntimeError, match="WORKSPACE"):
+        draft_topw(x, W, workspace_tensor=torch.empty(least - 1, dtype=torch.uint8, device="cuda"))

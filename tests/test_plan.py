@@ -24,6 +24,13 @@ def shapes():
                 for D in [64, 128]:
                     for L in [0, 1, 64, 1000, 32768]:
                         out.append((B, N, Hq, Hkv, D, L, 151936 if N < 100 else 1001))
+    # around one, four and sixteen sequences per lane of the even split, and past it
+    for B in [63, 64, 65, 200, 256, 257, 1000, 1024, 1025]:
+        for Hq, Hkv in [(4, 1), (8, 2), (16, 8), (3, 3)]:
+            for L in [64, 3000, 20000]:
+                out.append((B, 3, Hq, Hkv, 128 if B % 2 else 64, L, 1001))
+    # more key tiles than the even split takes
+    out += [(1, 8, 4, 1, 64, 1 << 25, 1001), (3, 8, 4, 1, 64, (1 << 25) - 9, 1001)]
     # more row blocks than the split-KV sync region holds: no split
     out += [(64, 512, 64, 8, 128, 1000, 1001), (512, 64, 32, 8, 128, 32768, 1001)]
     return out
