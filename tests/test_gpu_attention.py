@@ -53,8 +53,11 @@ FUZZ = [
     (3, 128, 32, 4, 128, 6000, [5999, 1234, 100], "random"),
     (1, 256, 64, 8, 64, 6000, [6000], "random"),
     (2, 128, 32, 4, 64, 6000, [6000, 37], "chain"),
-    # many short ragged sequences: the longest-first ranking holds two (40
-    # sequences) and eight (512 sequences) pairs per lane
+    # many short ragged sequences; on 8 KV heads the longest-first ranking holds
+    # two (70 sequences), four (250), eight (512) and sixteen (1000) pairs per lane
+    (70, 4, 8, 8, 64, 300, [(53 * i) % 301 for i in range(70)], "random"),
+    (250, 3, 8, 8, 64, 150, [(17 * i * i) % 151 for i in range(250)], "chain"),
+    (1000, 1, 8, 8, 64, 100, [(37 * i) % 101 for i in range(1000)], "random"),
     (40, 8, 8, 4, 64, 2048, [(97 * i * i + 13 * i) % 2049 for i in range(40)], "random"),
     (512, 2, 8, 8, 64, 200, [(31 * i) % 201 for i in range(512)], "random"),
 ]
