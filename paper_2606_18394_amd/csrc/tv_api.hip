@@ -62,19 +62,13 @@ static const tv::AttnPlan& attn_plan_of(int B, int N, int Hq, int Hkv, int D, in
   return last.plan;
 }
 
-// The plan that a call's workspace allows: the shape's, or the fixed split's
-// where that is enough; ok says whether either is.
+// The plan that a call's workspace allows; ok: there is one.
 static tv::AttnPlan attn_plan_within(int B, int N, int Hq, int Hkv, int D, int Lmax,
                                      const void* workspace, size_t bytes, bool& ok) {
-  auto fits = [&](const tv::AttnPlan& p) {
-    return p.ws_bytes == 0 || (workspace && bytes >= p.ws_bytes);
-  };
-  const tv::AttnPlan& p = attn_plan_of(B, N, Hq, Hkv, D, Lmax);
-  ok = fits(p);
-  if (ok) return p;
-  const tv::AttnPlan q = tv::attn_plan_fixed(B, N, Hq, Hkv, D, Lmax);
-  ok = fits(q);
-  return q;
+  tv::AttnPlan p = attn_plan_of(B, N, Hq, Hkv, D, Lmax);
+  if (!workspace) bytes = 0;
+  ok = p.ws_bytes <= bytes || tv::attn_plan_within(B, N, Hq, Hkv, D, Lmax, bytes, p);
+  return p;
 }
 
 static bool misaligned(const void* p) { return ((uintptr_t)p & 15u) != 0; }

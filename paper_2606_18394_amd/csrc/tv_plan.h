@@ -287,11 +287,11 @@ inline double attn_plan_cost(AttnPlan& p, int B, int Hkv, int D, int Lmax, int N
     };
     const double fused = 1.1 + fold(58.25e3, 233.0e3), second = 3.3 + waits + all / 4.0e6;
     t += (fused < second ? fused : second) + all / 5.5e6 + 1.0;
+    // more than 64 sequences: several per lane in the search for a work item
+    if (B > 64) t += B > 256 ? 5.0 : 2.0;
     // The kind of merge: by the workgroup whose chunk arrives last (one CU reads
     // 61 to 78 KB/us of partials), or by a second kernel that spreads it over
     // the GPU and starts when the slowest chunk is done (9 us for 33.5 MB).
-    // more than 64 sequences: several per lane in the search for a work item
-    if (B > 64) t += B > 256 ? 5.0 : 2.0;
     p.fused = 1.1 + fold(15.0e3, 78.0e3) <= 5.3 + waits + all / 4.0e6;
   }
   return t;
@@ -342,10 +342,8 @@ inline AttnPlan attn_plan_fixed(int B, int N, int Hq, int Hkv, int D, int Lmax) 
   return best;
 }
 
-inline AttnPlan attn_plan(int B, int N, int Hq, int Hkv, int D, int Lmax) {
-  // (the even split's quotients hold below 2^20 tiles)
-  if (cdiv(Lmax, kKeyTile) + cdiv(N, kKeyTile) >= kEvenTiles)
-    return attn_plan_fixed(B, N, Hq, Hkv, D, Lmax);
+// The cheapest plan of at most `most` bytes of workspace.
+inline AttnPlan attn_plan_search(int B, int N, int Hq, int Hkv, int D, int Lmax, size_t most) {
   AttnPlan best{};
   double best_cost = 0;
   bool have = false;
@@ -366,6 +364,7 @@ inline AttnPlan attn_plan(int B, int N, int Hq, int Hkv, int D, int Lmax) {
       const long long places = one.spread == 2 ? 128LL : 256LL;
       if (c > 0 && B > 64 && (long long)B * Hkv * one.nRB >= places * one.wg_per_cu) continue;
       AttnPlan p = c == 0 ? one : attn_plan_arr(B, N, Hq, Hkv, D, Lmax, k, cand[c]);
+      if (p.ws_bytes > most) continue;
       const double t = attn_plan_cost(p, B, Hkv, D, Lmax, N);
       if (!have || t < best_cost) {
         best = p;
@@ -375,6 +374,29 @@ inline AttnPlan attn_plan(int B, int N, int Hq, int Hkv, int D, int Lmax) {
     }
   }
   return best;
+}
+
+inline bool attn_even_tiles(int N, int Lmax) {
+  return cdiv(Lmax, kKeyTile) + cdiv(N, kKeyTile) < kEvenTiles;
+}
+
+inline AttnPlan attn_plan(int B, int N, int Hq, int Hkv, int D, int Lmax) {
+  // (the even split's quotients hold below 2^20 tiles)
+  return attn_even_tiles(N, Lmax) ? attn_plan_search(B, N, Hq, Hkv, D, Lmax, SIZE_MAX)
+                                  : attn_plan_fixed(B, N, Hq, Hkv, D, Lmax);
+}
+
+// The plan of a call whose workspace is too small for attn_plan's: the fixed
+// split's, or the cheapest within `bytes`, a smaller split or none.  That one
+// serves workspaces that hold a split at all, and every size where no workspace
+// was ever asked for (more than 64 sequences, caches of 2^20 tiles and more).
+// False: the workspace is refused.
+inline bool attn_plan_within(int B, int N, int Hq, int Hkv, int D, int Lmax, size_t bytes, AttnPlan& p) {
+  p = attn_plan_fixed(B, N, Hq, Hkv, D, Lmax);
+  if (p.ws_bytes <= bytes) return true;
+  if (bytes < kSyncBytes && B <= 64 && attn_even_tiles(N, Lmax)) return false;
+  p = attn_plan_search(B, N, Hq, Hkv, D, Lmax, bytes);
+  return true;
 }
 
 // Training-mask calls with several blocks to a workgroup (tv_attention.hip,

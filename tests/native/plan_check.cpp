@@ -1,6 +1,6 @@
 // Host-side check of the launch plans (tv_plan.h is plain C++): for each
-// shape on stdin ("B N Hq Hkv D Lmax V"), the plan a call gets and the fixed
-// split's plan that a call with less workspace falls back to.  Every launched
+// shape on stdin ("B N Hq Hkv D Lmax V"), the plan a call gets, the fixed split's
+// plan and those that calls with less workspace fall back to.  Every launched
 // workgroup is enumerated exactly as the kernels decode it: the decoded work
 // items are in range and cover every (b, g, rb, chunk) once, for the even split
 // with the chunks that a host copy of the kernels' search finds for ragged,
@@ -149,6 +149,23 @@ static bool check_even(const AttnPlan& p) {
   return true;
 }
 
+static bool check_plan(const AttnPlan& p) { return p.slots > 0 ? check_even(p) : check_fixed(p); }
+
+// Calls with less workspace than the plan asks for: what is refused, and that the
+// plans of the others stay within it.
+static bool check_within(const AttnPlan& p, const AttnPlan& fixed) {
+  const bool always = B > 64 || cdiv(Lmax, tv::kKeyTile) + cdiv(N, tv::kKeyTile) >= (1 << 20);
+  for (size_t limit : {p.ws_bytes, fixed.ws_bytes, p.ws_bytes / 2, tv::kSyncBytes + 1, tv::kSyncBytes, (size_t)1}) {
+    const size_t bytes = limit > 0 ? limit - 1 : 0;
+    if (bytes >= p.ws_bytes) continue;
+    AttnPlan q{};
+    const bool ok = tv::attn_plan_within(B, N, Hq, Hkv, D, Lmax, bytes, q);
+    if (ok != (fixed.ws_bytes <= bytes || bytes >= tv::kSyncBytes || always)) return false;
+    if (ok && (q.ws_bytes > bytes || !check_plan(q))) return false;
+  }
+  return true;
+}
+
 static bool check_vocab() {
   bool ok = true;
   for (int esize : {2, 4}) {
@@ -183,8 +200,8 @@ int main() {
   while (std::scanf("%d %d %d %d %d %d %d", &B, &N, &Hq, &Hkv, &D, &Lmax, &V) == 7) {
     ++cases;
     const AttnPlan p = tv::attn_plan(B, N, Hq, Hkv, D, Lmax);
-    const bool ok = (p.slots > 0 ? check_even(p) : check_fixed(p)) &&
-                    check_fixed(tv::attn_plan_fixed(B, N, Hq, Hkv, D, Lmax)) && check_vocab();
+    const AttnPlan fixed = tv::attn_plan_fixed(B, N, Hq, Hkv, D, Lmax);
+    const bool ok = check_plan(p) && check_fixed(fixed) && check_within(p, fixed) && check_vocab();
     std::printf("%s B=%d N=%d Hq=%d Hkv=%d D=%d L=%d V=%d S=%d slots=%d fused=%d RB=%d nRB=%d grid=%d spread=%d lds=%zu ws=%zu\n",
                 ok ? "OK" : "FAIL", B, N, Hq, Hkv, D, Lmax, V, p.S, p.slots, p.fused, p.RB, p.nRB,
                 p.grid, p.spread, p.lds_bytes, p.ws_bytes);
