@@ -84,6 +84,16 @@ struct AttnArgs {
   int cgroup;  // sequences sharing one cache (sequence b reads cache b / cgroup)
 };
 
+// The kernel's arguments, fetched (again) from where this is called on: what only
+// the epilogue needs then holds no scalar registers during the tile loop, whose
+// own would otherwise be spilled to vector lanes and read back at every tile.
+typedef const __attribute__((address_space(4))) AttnArgs LateArgs;
+__device__ __forceinline__ const LateArgs* late_args() {
+  const LateArgs* p = (const LateArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
 // Context rows of sequence b: its kv_len clamped to what the cache holds (in
 // the tree-tail layout behind room for the tree); a NULL kv_len means full.
 __device__ __forceinline__ int context_rows(const AttnArgs& a, int b) {
@@ -730,7 +740,7 @@ __device__ __forceinline__ void attend_tile(const unsigned char* kt_lds, const b
 // block has more row tiles than the workgroup has waves), so each lane
 // reads its rows' (m, l) once.
 template <int D, int RB, int kWaves>
-__device__ __forceinline__ void merge_chunks(const AttnArgs& a, size_t part0, int nval, int b,
+__device__ __forceinline__ void merge_chunks(const LateArgs* a, size_t part0, int nval, int b,
                                              int g, int r0, bool bad, int wave, int lane) {
   constexpr int DT = D / 16, NTG = RB / 16;
   constexpr bool kSplitCols = kWaves >= NTG;
@@ -745,7 +755,7 @@ __device__ __forceinline__ void merge_chunks(const AttnArgs& a, size_t part0, in
 #pragma unroll
   for (int k = 0; k < NPW; ++k) {
     const int ntg = kSplitCols ? wave % NTG : wave + k * kWaves;
-    if (r0 + ntg * 16 >= a.M) continue;  // no rows
+    if (r0 + ntg * 16 >= a->M) continue;  // no rows
     const int dt0 = kSplitCols ? wave / NTG : 0;
     const int row = ntg * 16 + l16;
     float m = -INFINITY, l = 0.f;
@@ -759,10 +769,10 @@ __device__ __forceinline__ void merge_chunks(const AttnArgs& a, size_t part0, in
       for (int u = 0; u < UB; ++u)
         if (s0 + u < nval) {
           const size_t ps = part0 + s0 + u;
-          ml[u] = load_dev(&a.ws_ml[ps * RB + row]);
+          ml[u] = load_dev(&a->ws_ml[ps * RB + row]);
 #pragma unroll
           for (int j = 0; j < DPW; ++j)
-            ov[u][j] = load_dev(&a.ws_o[(ps * DT * NTG + (dt0 + j * WPN) * NTG + ntg) * 64 + lane]);
+            ov[u][j] = load_dev(&a->ws_o[(ps * DT * NTG + (dt0 + j * WPN) * NTG + ntg) * 64 + lane]);
         }
       wait_all_vm();
 #pragma unroll
@@ -785,9 +795,9 @@ __device__ __forceinline__ void merge_chunks(const AttnArgs& a, size_t part0, in
         }
     }
     const int r = r0 + row;
-    if (r < a.M) {
-      const int node = r / a.G, h = g * a.G + r % a.G;
-      __bf16* op = a.out + ((size_t)(b * a.N + node) * a.Hq + h) * D + 4 * g4;
+    if (r < a->M) {
+      const int node = r / a->G, h = g * a->G + r % a->G;
+      __bf16* op = a->out + ((size_t)(b * a->N + node) * a->Hq + h) * D + 4 * g4;
       const float inv = 1.f / l;
 #pragma unroll
       for (int j = 0; j < DPW; ++j) store_out4(op + 16 * (dt0 + j * WPN), acc[j], inv, bad);
@@ -1087,6 +1097,7 @@ void attn_main(AttnArgs a) {
                              bits, g4, l16);
   }
 
+  const LateArgs* z = late_args();
   float lsum[NT];
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) lsum[nt] = lacc[nt][0];
@@ -1094,43 +1105,53 @@ void attn_main(AttnArgs a) {
   // Only chunks that hold tiles take part in a merge, nval of them; a row
   // block that is one chunk needs none and writes its output here.
   const int nval = (T + chunk - 1) / chunk;
-  const bool whole = a.S == 1 || nval == 1;
-  const int bg = b * a.Hkv + g;
-  const size_t grp = (size_t)bg * a.nRB + rb;  // row block id
+  const bool whole = z->S == 1 || nval == 1;
+  const int bg = b * z->Hkv + g;
+  const size_t grp = (size_t)bg * z->nRB + rb;  // row block id
 
-  // Final values of one 16x16 fragment (dt, ntg) of this workgroup's rows:
-  // either the normalised bf16 output (single chunk) or the chunk partial.
-  // Fragments wholly past the last row are neither stored here nor read by the
-  // merges, which the plan's cost counts on (2 x 3 nodes, 32 heads on 8, 1361
-  // rows: 19.0 -> 16.9 us; 64 x 2 nodes 55.5 -> 50.8; 16 x 33 nodes 53.0 -> 51.2).
-  auto emit = [&](int dt, int ntg, const f32x4& acc, float mstar, float l) {
-    const int row = ntg * 16 + l16;
-    if (r0 + ntg * 16 >= a.M) return;
-    if (whole) {
-      const int r = r0 + row;
-      if (r < a.M) {
-        const int node = r / a.G, h = g * a.G + r % a.G;
-        store_out4(a.out + ((size_t)(b * a.N + node) * a.Hq + h) * D + 16 * dt + 4 * g4, acc,
-                   1.f / l, invalid != 0);
-      }
-    } else {
-      f32x4* po = &a.ws_o[((size_t)(part0 + s) * DT * NTG + dt * NTG + ntg) * 64 + lane];
-      float2* pml = &a.ws_ml[(size_t)(part0 + s) * RB + row];
-      if (a.fused) {  // read by another workgroup of this kernel
-        store_dev(po, acc);
-        if (dt == 0 && g4 == 0) store_dev(pml, make_float2(mstar, l));
-      } else {        // read by the merge kernel
-        *po = acc;
-        if (dt == 0 && g4 == 0) *pml = make_float2(mstar, l);
-      }
+  // Final values of 16x16 fragments (dt, ntg) of this workgroup's rows: either
+  // the normalised bf16 output (single chunk) or the chunk partial.  Fragments
+  // wholly past the last row are neither stored here nor read by the merges,
+  // which the plan's cost counts on (2 x 3 nodes, 32 heads on 8, 1361 rows: 19.0
+  // -> 16.9 us; 64 x 2 nodes 55.5 -> 50.8; 16 x 33 nodes 53.0 -> 51.2).
+  auto rows_at = [&](int ntg) { return r0 + ntg * 16 < z->M; };
+  auto emit_out = [&](int dt, int ntg, const f32x4& acc, float l) {
+    const int r = r0 + ntg * 16 + l16;
+    if (r < z->M) {
+      const int node = r / z->G, h = g * z->G + r % z->G;
+      store_out4(z->out + ((size_t)(b * z->N + node) * z->Hq + h) * D + 16 * dt + 4 * g4, acc,
+                 1.f / l, invalid != 0);
+    }
+  };
+  auto emit_part = [&](bool dev, int dt, int ntg, const f32x4& acc, float mstar, float l) {
+    f32x4* po = &z->ws_o[((size_t)(part0 + s) * DT * NTG + dt * NTG + ntg) * 64 + lane];
+    float2* pml = &z->ws_ml[(size_t)(part0 + s) * RB + ntg * 16 + l16];
+    if (dev) {  // read by another workgroup of this kernel
+      store_dev(po, acc);
+      if (dt == 0 && g4 == 0) store_dev(pml, make_float2(mstar, l));
+    } else {    // read by the merge kernel
+      *po = acc;
+      if (dt == 0 && g4 == 0) *pml = make_float2(mstar, l);
     }
   };
 
   if (WK == 1) {
+    // The kind of store is settled once per row tile, not at every fragment.
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
+    for (int nt = 0; nt < NT; ++nt) {
+      const int ntg = wr * NT + nt;
+      if (!rows_at(ntg)) break;
+      if (whole) {
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) emit(dt, wr * NT + nt, o[dt][nt], m[nt], lsum[nt]);
+        for (int dt = 0; dt < DT; ++dt) emit_out(dt, ntg, o[dt][nt], lsum[nt]);
+      } else if (z->fused) {
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) emit_part(true, dt, ntg, o[dt][nt], m[nt], lsum[nt]);
+      } else {
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) emit_part(false, dt, ntg, o[dt][nt], m[nt], lsum[nt]);
+      }
+    }
   } else {
     // ---- merge the WK key groups of each row group (same rows, disjoint keys)
     __syncthreads();  // rings and tree tables are dead from here on
@@ -1148,6 +1169,7 @@ void attn_main(AttnArgs a) {
     __syncthreads();
     for (int f = wk; f < DT * NT; f += WK) {
       const int dt = f / NT, nt = f % NT;
+      if (!rows_at(wr * NT + nt)) continue;
       const int rw = nt * 16 + l16;  // row within the wave's 32
       float mw[WK], mstar = -INFINITY;
 #pragma unroll
@@ -1163,10 +1185,12 @@ void attn_main(AttnArgs a) {
         l += e * mlbuf[(k * WR + wr) * kRowsPerWave + rw].y;
         acc += e * obuf[(((k * WR + wr) * DT + dt) * NT + nt) * 64 + lane];
       }
-      emit(dt, wr * NT + nt, acc, mstar, l);
+      if (whole) emit_out(dt, wr * NT + nt, acc, l);
+      else if (z->fused) emit_part(true, dt, wr * NT + nt, acc, mstar, l);
+      else emit_part(false, dt, wr * NT + nt, acc, mstar, l);
     }
   }
-  if (whole || !a.fused) return;
+  if (whole || !z->fused) return;
 
   // ---- fused split-KV merge: the chunk that arrives last merges its row
   // block.  Every workgroup publishes its partial (device-scope stores,
@@ -1174,20 +1198,20 @@ void attn_main(AttnArgs a) {
   // completes the count merges and resets the counter for the next call.
   __shared__ int s_last;
   if (has_tree && tid == 0)  // every row block has a chunk with tree tiles
-    __hip_atomic_store(a.tree_bad + grp, invalid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(z->tree_bad + grp, invalid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   wait_all_vm();
   __syncthreads();
   if (tid == 0) {
     const unsigned int before =
-        __hip_atomic_fetch_add(a.arrived + grp, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(z->arrived + grp, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const bool last = before + 1 == (unsigned int)nval;
-    if (last) __hip_atomic_store(a.arrived + grp, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (last) __hip_atomic_store(z->arrived + grp, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     s_last = last;
   }
   __syncthreads();
   if (!s_last) return;
-  const bool bad = __hip_atomic_load(a.tree_bad + grp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-  merge_chunks<D, RB, kWaves>(a, part0, nval, b, g, r0, bad, wave, lane);
+  const bool bad = __hip_atomic_load(z->tree_bad + grp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+  merge_chunks<D, RB, kWaves>(z, part0, nval, b, g, r0, bad, wave, lane);
 }
 
 // Training mask, several blocks to a workgroup.  The A blocks of an example read
