@@ -1278,10 +1278,10 @@ void attn_packed(PackArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int lane = threadIdx.x & 63, g4 = lane >> 4, l16 = lane & 15;
   const int wr = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  // (pack, KV head) pairs go to the XCDs in turn, so that an XCD keeps to few
-  // heads' context; within that the packs of the largest anchors come first
-  const int qq = (int)(blockIdx.x / kXcds) * kXcds + (int)(blockIdx.x % kXcds);
-  const int g = qq % a.Hkv, u = qq / a.Hkv;
+  // KV heads in turn, then examples; the packs of the largest anchors come first.
+  // Workgroups go to the XCDs in turn too, so an XCD reads the context of Hkv /
+  // gcd(8, Hkv) heads: one with 8 of them, all where their number is odd.
+  const int g = (int)blockIdx.x % a.Hkv, u = (int)blockIdx.x / a.Hkv;
   const int b = u % a.B, p = u / a.B;
   if (p >= a.packs) return;
 
