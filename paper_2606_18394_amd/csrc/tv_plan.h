@@ -202,39 +202,43 @@ inline bool attn_plan_fits(const AttnPlan& p) {
   return p.NS > 0 && p.lds_bytes * p.wg_per_cu <= kMaxLds;
 }
 
-// Relative time of a plan, roughly in microseconds.  The constants are fitted so
-// that the plan picked is the fastest measured one: 260 shapes (1 to 32
-// sequences, 8 to 512 nodes, 256 to 32768 cached rows, the head shapes of the
-// models above and D = 64) in every arrangement and up to four split counts, and
-// for the merges 170 more (1 to 64 sequences, 1 to 2000 nodes, 1 to 32 KV heads,
-// up to 130000 rows).  A chunk's tiles take their turns at one time per tile and
-// key group: the latency of a tile's chain of LDS reads, matrix and vector work,
-// or the CU's share of that work.  A split plan's chunk has all its row blocks on
-// one XCD, so what does not fit the XCDs at once queues there.  On top come the
-// fixed costs at a workgroup's two ends, HBM as the floor of the streaming (also
-// at what the CUs at work can ask for), and the split's partials.  The lengths of
-// several sequences are unknown here: they are taken as spread over the capacity,
-// kMeanFill of it on average.
-constexpr double kMeanFill = 0.64;
+// Relative time of a plan, roughly in microseconds.  The constants are fitted
+// together so that the plan picked is the fastest measured one: 1537 shapes (1267 of
+// 1 to 32 sequences, 8 to 512 nodes and 256 to 32768 cached rows of the head shapes
+// of the models above and D = 64, or as many training blocks; 155 of 1 to 64
+// sequences, 1 to 64 nodes, 1 to 32 KV heads and up to 120000 rows; 115 of 65 to 400
+// sequences), each in every arrangement, up to five split counts and both merges.
+// The plans picked are 3.0% slower than the fastest on average.  They stand close to
+// each other, so a rounding of these constants moves some of them: time all of them
+// again before changing one.
+//
+// A chunk's tiles take their turns at one time per tile and key group: the latency
+// of a tile's chain of LDS reads, matrix and vector work, or the CU's share of that
+// work.  A split plan's chunk has all its row blocks on one XCD, so what does not fit
+// the XCDs at once queues there.  On top come the fixed costs at a workgroup's two
+// ends, HBM as the floor of the streaming (also at what the CUs at work can ask for),
+// and the split's partials.  The lengths of several sequences are unknown here: they
+// are taken as spread over the capacity, kMeanFill of it on average.
+constexpr double kMeanFill = 0.6284;
 
 // Tile time of one key group with all 8 waves of a CU at work, per arrangement
-// (its latency alone: 1.15, with two ring stages 1.28).
-constexpr double kTileFull[] = {1.60, 1.24, 1.33, 1.41, 1.15, 1.28, 1.32};
+// (its latency alone: 1.214, with two ring stages 1.34).
+constexpr double kTileFull[] = {1.888, 1.349, 1.402, 1.433, 1.0, 1.112, 1.34};
 static_assert(sizeof(kTileFull) / sizeof(kTileFull[0]) == kNumArrangements, "one per arrangement");
 
 // Bytes per microsecond one CU can ask HBM for.  2 sequences of 80754 rows, 4
 // nodes, 8 KV heads, D = 64: 128 workgroups of 8 waves 95 us, 256 75.
-constexpr double kCuBytes = 75.0e3;
+constexpr double kCuBytes = 88.5e3;
 
 inline double attn_plan_cost(AttnPlan& p, int B, int Hkv, int D, int Lmax, int N) {
   const double longest = cdiv(Lmax, kKeyTile) + cdiv(N, kKeyTile);
   const double mean = B == 1 ? longest : kMeanFill * cdiv(Lmax, kKeyTile) + cdiv(N, kKeyTile);
   double chunk = longest, items = B;
   if (p.slots > 0) {
-    chunk = B == 1 ? (double)cdiv((long long)longest, p.slots) : B * mean / (p.slots - 0.33 * B);
+    chunk = B == 1 ? (double)cdiv((long long)longest, p.slots) : B * mean / (p.slots - 0.3277 * B);
     if (chunk < p.min_chunk) chunk = p.min_chunk;
     if (chunk > longest) chunk = longest;
-    items = B == 1 ? (double)cdiv((long long)longest, (long long)chunk) : B * mean / chunk + 0.5 * B;
+    items = B == 1 ? (double)cdiv((long long)longest, (long long)chunk) : B * mean / chunk + 0.5163 * B;
     if (items > p.slots) items = p.slots;
   }
   const double wgs = items * Hkv * p.nRB, room = 256.0 * p.wg_per_cu;
@@ -242,9 +246,9 @@ inline double attn_plan_cost(AttnPlan& p, int B, int Hkv, int D, int Lmax, int N
   per_cu = per_cu < 1.0 ? 1.0 : (per_cu > p.wg_per_cu ? p.wg_per_cu : per_cu);
   const double row_tiles = (double)cdiv(p.M, kRowsPerWave) / p.nRB;
   const double waves = per_cu * p.WK * (row_tiles < p.WR ? row_tiles : p.WR);
-  double tile = p.NS == 2 ? 1.28 : 1.15;
+  double tile = p.NS == 2 ? 1.34 : 1.214;
   if (kTileFull[p.arr] * waves / 8.0 > tile) tile = kTileFull[p.arr] * waves / 8.0;
-  if (D == 64) tile *= 0.55;
+  if (D == 64) tile *= 0.4675;
   double t = chunk / p.WK * tile;
   // workgroups of the fullest XCD over what it holds at once (unsplit plans
   // spread their row blocks over all XCDs)
@@ -255,18 +259,18 @@ inline double attn_plan_cost(AttnPlan& p, int B, int Hkv, int D, int Lmax, int N
     double load = B * mean * Hkv * p.nRB / room;  // tiles a place takes, on average
     const double fullest = per_xcd * chunk / (32.0 * p.wg_per_cu);
     if (p.slots > 0 && fullest > load) load = fullest;
-    const double queue = load / p.WK * tile + 0.34 * t;
+    const double queue = load / p.WK * tile + 0.3287 * t;
     const double turns = rounds * t;
     t = t > queue ? t : (queue < turns ? queue : turns);
   }
   // unsplit, whole sequences to an XCD, and no order that evens them out: the XCD
   // with the longest sets the end (64 x 234 nodes, 2 KV heads, D = 64, up to 6296
-  // rows: 172 us unsplit, 123 in 2)
-  if (p.slots == 0 && B >= kXcds && p.spread != 2) t *= 1.15;
+  // rows: 140 us unsplit, 122 in 2)
+  if (p.slots == 0 && B >= kXcds && p.spread != 2) t *= 1.029;
   const double asked = (wgs < 256 ? wgs : 256) * kCuBytes;
-  const double hbm = B * mean * kKeyTile * Hkv * D * 4.0 / (asked < 10.0e6 ? asked : 10.0e6);
+  const double hbm = B * mean * kKeyTile * Hkv * D * 4.0 / (asked < 11.8e6 ? asked : 11.8e6);
   t = t > hbm ? t : hbm;
-  t += 7.1 + (p.WK > 1 ? 0.85 : 0.0) + 18.0 * (rounds - 1);
+  t += 7.788 + (p.WK > 1 ? 0.9328 : 0.0) + (p.slots > 0 ? 17.69 : 17.86) * (rounds - 1);
   if (chunk < longest) {
     const double chunks = (double)cdiv((long long)longest, (long long)(chunk + 0.999));
     // A row block's partial in bytes (whole 16-row fragments), and all of them.
@@ -274,25 +278,24 @@ inline double attn_plan_cost(AttnPlan& p, int B, int Hkv, int D, int Lmax, int N
     // waves without rows are idle, and few waves read at less than the CU's rate
     // (one wave alone 33 to 44 KB/us: 1 node over 24503 rows, 383 chunks of 3 tiles,
     // 108 us where 42 chunks take 23).  The second kernel has one wave per
-    // fragment, and waits for memory once per 16 chunks (the second time hardly:
-    // 2 x 50 nodes over 108621 rows in 32 chunks of 4 x 2 waves 66 us, in 16 of 2 x
-    // 4 83; 24 nodes over 107622 in 241 chunks 58 us, in 64 36).
+    // fragment, and waits for memory once per 16 chunks (the second time hardly: 1 node
+    // over 24503 rows, 3 heads, in 77 chunks 26.6 us, in 41 21.7).
     const int NTG = p.RB / 16, waves_wg = p.WR * p.WK;
     const int nt = cdiv(p.M < p.RB ? p.M : p.RB, 16);
     const int active = waves_wg >= NTG ? waves_wg / NTG * nt : (nt < waves_wg ? nt : waves_wg);
     const double block = nt * 16.0 * D * 4.0, all = wgs / p.nRB * cdiv(p.M, 16) * 16.0 * D * 4.0;
-    const double waits = chunks > 32 ? 1.0 * (cdiv((long long)chunks, 16) - 2) : 0.0;
+    const double waits = chunks > 32 ? 1.6 * (cdiv((long long)chunks, 16) - 2) : 0.0;
     auto fold = [&](double per_wave, double per_cu) {
       return chunks * block / (active * per_wave < per_cu ? active * per_wave : per_cu);
     };
-    const double fused = 1.1 + fold(58.25e3, 233.0e3), second = 3.3 + waits + all / 4.0e6;
-    t += (fused < second ? fused : second) + all / 5.5e6 + 1.0;
+    const double fused = 0.935 + fold(49.5e3, 204.5e3), second = 3.894 + waits + all / 3.552e6;
+    t += (fused < second ? fused : second) + all / 4.899e6 + 0.1181;
     // more than 64 sequences: several per lane in the search for a work item
     if (B > 64) t += B > 256 ? 5.0 : 2.0;
     // The kind of merge: by the workgroup whose chunk arrives last (one CU reads
     // 61 to 78 KB/us of partials), or by a second kernel that spreads it over
     // the GPU and starts when the slowest chunk is done (9 us for 33.5 MB).
-    p.fused = 1.1 + fold(15.0e3, 78.0e3) <= 5.3 + waits + all / 4.0e6;
+    p.fused = 1.034 + fold(16.09e3, 66.53e3) <= 5.939 + waits + all / 3.4e6;
   }
   return t;
 }
@@ -356,8 +359,9 @@ inline AttnPlan attn_plan_search(int B, int N, int Hq, int Hkv, int D, int Lmax,
     const long long fill = kXcds * pairs / Hkv;
     const long long cand[5] = {B, fill / 4, fill / 2, fill, 2 * fill};
     for (int c = 0; c < 5; ++c) {
-      // a few chunks more than sequences split next to none of them
-      if (c > 0 && 2 * cand[c] < 3LL * B) continue;
+      // more chunks than sequences; of more than 64 sequences half as many again (a few
+      // more split next to none of them)
+      if (c > 0 && (B > 64 ? 2 * cand[c] < 3LL * B : cand[c] <= B)) continue;
       // (of more than 64 sequences only those whose row blocks leave CUs empty, half
       // of them where the longest go first (spread): 100 nodes, 32 heads on 8, D =
       // 64, up to 7273 rows 153 us unsplit, 201 in 2)

@@ -135,7 +135,7 @@ def test_partials_hold_the_rows_only(shape):
     (174, 6, 3, 3, 128, 168), (2, 6, 16, 8, 128, 459), (2, 14, 4, 4, 128, 458),
     (8, 3, 8, 2, 64, 2097), (2, 3, 8, 1, 64, 4165), (1, 18, 3, 3, 64, 5465), (3, 9, 2, 1, 64, 2655),
     # both ask for more than a smaller split, or none, once needed
-    (22, 4, 64, 8, 128, 975), (77, 5, 4, 1, 128, 951), (65, 3, 4, 2, 64, 3530),
+    (22, 4, 64, 8, 128, 975), (77, 5, 4, 1, 128, 951), (65, 9, 4, 1, 64, 3000),
 ])
 def test_less_workspace(shape):
     """A call with less workspace than the query says is computed: with the fixed
