@@ -94,17 +94,17 @@ __device__ __forceinline__ const LateArgs* late_args() {
   return p;
 }
 
-// Context rows of sequence b: its kv_len (asked_rows) clamped to what the cache
-// holds (in the tree-tail layout behind room for the tree); a NULL kv_len means full.
-__device__ __forceinline__ int asked_rows(const AttnArgs& a, int b) {
-  return a.kv_len ? a.kv_len[b] : INT32_MAX;
-}
-__device__ __forceinline__ int within_cache(const AttnArgs& a, int kvl) {
+// Context rows of sequence b: its kv_len clamped to what the cache holds (in
+// the tree-tail layout behind room for the tree); a NULL kv_len means full.
+__device__ __forceinline__ int context_rows(const AttnArgs& a, int b) {
   const int cap = a.tail ? a.Lmax - a.N : a.Lmax;
+  const int kvl = a.kv_len ? a.kv_len[b] : cap;
   return kvl < 0 ? 0 : (kvl > cap ? cap : kvl);
 }
-__device__ __forceinline__ int context_rows(const AttnArgs& a, int b) {
-  return within_cache(a, asked_rows(a, b));
+// The same from a kv_len asked for earlier (any value for a NULL one).
+__device__ __forceinline__ int context_rows_of(const AttnArgs& a, int asked) {
+  const int cap = a.tail ? a.Lmax - a.N : a.Lmax;
+  return a.kv_len && asked < cap ? max(asked, 0) : cap;
 }
 
 // The key tiles a row block attends over, behind kvl context rows and up to
@@ -235,8 +235,9 @@ struct EvenItem {
 };
 
 // One sequence: the item's number is the chunk's.
+template <bool kAsked>
 __device__ __forceinline__ EvenItem even_one(const AttnArgs& a, int item, int asked) {
-  const int kvl = within_cache(a, asked);
+  const int kvl = kAsked ? context_rows_of(a, asked) : context_rows(a, 0);
   const int t = segment(a, kvl, a.N - 1).T;
   const int chunk = max(a.min_chunk, ceil_div(t, a.slots, a.rslots));
   return EvenItem{chunk, 0, item * chunk < t ? item : -1, 0, kvl};
@@ -304,10 +305,11 @@ __device__ __forceinline__ EvenItem even_lanes(const AttnArgs& a, int item, int 
 }
 
 // Work item `item` of the batch, or (item < 0) what concerns sequence b; asked: the
-// first sequence's asked_rows.
+// first sequence's kv_len where kAsked, else of no use.
+template <bool kAsked>
 __device__ __forceinline__ EvenItem even_split(const AttnArgs& a, int item, int b, int asked) {
   static_assert(kEvenSequences == 16 * 64, "sequences per lane");
-  if (a.B == 1) return even_one(a, item, asked);
+  if (a.B == 1) return even_one<kAsked>(a, item, asked);
   if (a.B <= 64) return even_lanes<1>(a, item, b);
   return a.B <= 256 ? even_lanes<4>(a, item, b) : even_lanes<16>(a, item, b);
 }
@@ -835,13 +837,17 @@ void attn_main(AttnArgs a) {
   WorkItem it{};
   int chunk = a.chunk, kvl, part0;  // part0: the row block's first chunk partial
   // One sequence's length is on its way while the work item is found (64 nodes over
-  // 4096 rows 18.1 -> 17.8 us).
-  const int asked = asked_rows(a, 0);
-  asm volatile("" ::: "memory");
+  // 4096 rows 18.04 -> 17.80 us).  Not with one key group, whose plans have long
+  // chunks: there 512 nodes over 8192 rows took 148.3 us so, and 147.7 without.
+  int asked = 0;
+  if constexpr (WK > 1) {
+    if (a.kv_len) asked = a.kv_len[0];
+    asm volatile("" ::: "memory");
+  }
   if (a.slots > 0) {
     const int item = even_item(blockIdx.x, a.slots, a.nRB, a.Hkv, it);
     if (item < 0) return;
-    const EvenItem ev = even_split(a, item, 0, asked);
+    const EvenItem ev = even_split<(WK > 1)>(a, item, 0, asked);
     if (ev.s < 0) return;
     it.b = ev.b;
     it.s = ev.s;
@@ -1491,7 +1497,7 @@ __global__ __launch_bounds__(256) void attn_combine(AttnArgs a) {
   size_t base = (size_t)(bg * a.nRB + rb) * a.S;
   int nslot = a.S;
   if (a.slots > 0) {
-    if (a.B > 1) ev = even_split(a, -1, b, 0);
+    if (a.B > 1) ev = even_split<false>(a, -1, b, 0);
     base = (size_t)(g * a.nRB + rb) * a.slots + ev.first;
     nslot = a.slots - ev.first;
   }
@@ -1505,7 +1511,7 @@ __global__ __launch_bounds__(256) void attn_combine(AttnArgs a) {
       ov0[u] = a.ws_o[((base + u) * DT * NTG + dt * NTG + ntg) * 64 + lane];
     }
   if (a.slots == 0) ev.kvl = context_rows(a, b);
-  else if (a.B == 1) ev = even_one(a, 0, asked_rows(a, 0));
+  else if (a.B == 1) ev = even_one<false>(a, 0, 0);
   const int T = segment(a, ev.kvl, i_hi).T;
   int nval = (T + ev.chunk - 1) / ev.chunk;
   if (nval == 1) return;  // written by its only chunk
